@@ -18,10 +18,12 @@
 // l%16) is exactly the B-operand layout the next layer needs: activations
 // never leave registers between layers.
 //
-// Training runs on the vector ALUs in float32: one workgroup takes 64 samples,
-// keeps activations in LDS, and writes its partial gradient; a second kernel
-// sums the partials in a fixed order and applies Adam to the float32 master
+// Training runs on the matrix cores in float32 (k_mlp_grad): a workgroup takes
+// tiles of 64 samples and writes one partial gradient; a second kernel sums
+// the partials in a fixed order and applies Adam to the float32 master
 // weights, refreshing their half copy.
+#include <algorithm>
+
 #include "ftcg_internal.h"
 #include "mlp_internal.h"
 
@@ -436,143 +438,239 @@ __global__ __launch_bounds__(256) void k_learned_weights(const WSample<2>* __res
 // training
 // ---------------------------------------------------------------------------
 
-constexpr int TS = 64;   // samples per training workgroup
+constexpr int TS = 64;         // samples per training tile
+constexpr int TG_MAX = 512;    // training workgroups at most: two per compute unit (LDS)
+constexpr int PW = HW + 4;     // LDS row pitches: 4 rows apart are 16 banks apart, rows 16 bytes
+constexpr int PX = NF + 4;
 
-// partial gradient of the mean squared error over one workgroup's samples.
-// Minibatch `mb` holds samples j = mb + nmb * s, s in [0, batch) (and j < m).
-__global__ __launch_bounds__(256) void k_mlp_grad(const float* __restrict__ X, const float* __restrict__ T,
-                                                  int64_t m, int64_t mb, int64_t nmb, int64_t batch,
-                                                  const float* __restrict__ P, int fp16,
-                                                  float* __restrict__ partial) {
-  __shared__ float sW1[NF * HW], sW2[HW * HW], sW3[HW], sb1[HW], sb2[HW];
-  __shared__ float sX[TS][NF + 1];
-  __shared__ float sZ1[TS][HW + 1], sH1[TS][HW + 1], sZ2[TS][HW + 1];
-  __shared__ float sdy[TS], sloss[TS];
-  const int tid = threadIdx.x;
+// Partial gradient of the mean squared error over one workgroup's tiles of
+// 64 samples (tiles blockIdx, blockIdx + gridDim, ...). Minibatch `mb` holds
+// samples j = mb + nmb * s, s in [0, batch) (and j < m).
+//
+// The five products of a tile run on the matrix cores in float32
+// (v_mfma_f32_16x16x4_f32: float32 products and sums, as on the vector ALUs).
+// A wavefront takes 16 samples through the forward pass and back to dz1 with
+// the products formed transposed (Z^T = W^T X^T): the accumulator layout
+// (lane l: neurons 16t + 4(l/16) + r of sample l%16) is the B operand of the
+// next product when the contraction runs in the order k-step (t, r) ->
+// neurons 16t + 4g + r of lane group g, so activations stay in registers. The
+// weight gradients contract over samples: h1, dz2, then dz1 pass through LDS,
+// and every wavefront keeps its 16 x 64 block of dW2 and 32 x 16 block of dW1
+// in accumulators over all its tiles. What bounds it: 256 matrix
+// instructions of 32 cycles per tile and wavefront, 14 us of the chip's
+// matrix cores at 65536 samples; measured 43 us there, against 195 us
+// for one tile per workgroup with every product on the vector ALUs.
+template <bool HALF>
+__global__ __launch_bounds__(256, 2) void k_mlp_grad(const float* __restrict__ X, const float* __restrict__ T,
+                                                     int64_t m, int64_t mb, int64_t nmb, int64_t batch,
+                                                     const float* __restrict__ P, int64_t ntile,
+                                                     float* __restrict__ partial) {
+  __shared__ __align__(16) float sW1[NF * PW], sW2[HW * PW], sX[TS * PX], sA[TS * PW], sB[TS * PW];
+  __shared__ __align__(16) float sV[3][HW];   // b1, b2, W3
+  const int tid = threadIdx.x, w = tid >> 6, c = tid & 15, g = (tid >> 4) & 3;
+  auto rh = [](float v) { return HALF ? round_h(v) : v; };
+  for (int e = tid; e < NF * HW; e += 256) sW1[(e >> 6) * PW + (e & 63)] = rh(P[MLP_W1 + e]);
+  for (int e = tid; e < HW * HW; e += 256) sW2[(e >> 6) * PW + (e & 63)] = rh(P[MLP_W2 + e]);
+  if (tid < HW) {
+    sV[0][tid] = P[MLP_B1 + tid];
+    sV[1][tid] = P[MLP_B2 + tid];
+    sV[2][tid] = rh(P[MLP_W3 + tid]);
+  }
   const float b3 = P[MLP_B3];
-  for (int e = tid; e < NF * HW; e += 256) sW1[e] = fp16 ? round_h(P[MLP_W1 + e]) : P[MLP_W1 + e];
-  for (int e = tid; e < HW * HW; e += 256) sW2[e] = fp16 ? round_h(P[MLP_W2 + e]) : P[MLP_W2 + e];
-  if (tid < HW) {
-    sW3[tid] = fp16 ? round_h(P[MLP_W3 + tid]) : P[MLP_W3 + tid];
-    sb1[tid] = P[MLP_B1 + tid];
-    sb2[tid] = P[MLP_B2 + tid];
-  }
-  const int64_t s0 = (int64_t)blockIdx.x * TS;
-  for (int e = tid; e < TS * NF; e += 256) {
-    const int s = e / NF, q = e % NF;
-    const int64_t sg = s0 + s, j = mb + nmb * sg;
-    float v = (sg < batch && j < m) ? X[j * NF + q] : 0.f;
-    sX[s][q] = fp16 ? round_h(v) : v;
-  }
+  const float4_t zero = {0.f, 0.f, 0.f, 0.f};
+  float4_t gW2[4] = {zero, zero, zero, zero}, gW1[2] = {zero, zero};
+  float4_t gb1[4] = {zero, zero, zero, zero}, gb2[4] = {zero, zero, zero, zero}, gW3[4] = {zero, zero, zero, zero};
+  float gb3 = 0.f, loss = 0.f;
   __syncthreads();
-  const int s = tid >> 2, n0 = (tid & 3) * 16;
-  // layer 1
-  for (int c = 0; c < 16; ++c) {
-    const int n = n0 + c;
-    float z = sb1[n];
-    for (int q = 0; q < NF; ++q) z += sX[s][q] * sW1[q * HW + n];
-    sZ1[s][n] = z;
-    const float h = silu_f(z);
-    sH1[s][n] = fp16 ? round_h(h) : h;
-  }
-  __syncthreads();
-  // layer 2
-  for (int c = 0; c < 16; ++c) {
-    const int n = n0 + c;
-    float z = sb2[n];
-    for (int q = 0; q < HW; ++q) z += sH1[s][q] * sW2[q * HW + n];
-    sZ2[s][n] = z;
-  }
-  __syncthreads();
-  // output, residual
-  if (tid < TS) {
-    const int64_t sg = s0 + tid, j = mb + nmb * sg;
+  for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
+    const int64_t sg = tile * TS + w * 16 + c, j = mb + nmb * sg;
     const bool valid = sg < batch && j < m;
-    float y = b3;
-    for (int q = 0; q < HW; ++q) {
-      const float h = silu_f(sZ2[tid][q]);
-      y += (fp16 ? round_h(h) : h) * sW3[q];
+    float4_t x[2] = {zero, zero};
+    if (valid) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[t][r] = rh(X[j * NF + 16 * t + 4 * g + r]);
     }
-    const float r = valid ? y - T[j] : 0.f;
-    sdy[tid] = 2.f * r / (float)batch;
-    sloss[tid] = r * r;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) *reinterpret_cast<float4_t*>(&sX[(w * 16 + c) * PX + 16 * t + 4 * g]) = x[t];
+    // layer 1
+    float4_t z1[4], h[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) z1[t] = *reinterpret_cast<const float4_t*>(&sV[0][16 * t + 4 * g]);
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          z1[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(sW1[(16 * k + 4 * g + r) * PW + 16 * t + c], x[k][r], z1[t],
+                                                       0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) h[t][r] = rh(silu_f(z1[t][r]));
+      *reinterpret_cast<float4_t*>(&sA[(w * 16 + c) * PW + 16 * t + 4 * g]) = h[t];
+    }
+    // layer 2
+    float4_t z2[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) z2[t] = *reinterpret_cast<const float4_t*>(&sV[1][16 * t + 4 * g]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          z2[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(sW2[(16 * k + 4 * g + r) * PW + 16 * t + c], h[k][r], z2[t],
+                                                       0, 0, 0);
+    // output (each lane group holds a quarter of the neurons), residual
+    float y = 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float4_t w3 = *reinterpret_cast<const float4_t*>(&sV[2][16 * t + 4 * g]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        h[t][r] = rh(silu_f(z2[t][r]));
+        y += h[t][r] * w3[r];
+      }
+    }
+    y += __shfl_xor(y, 16);
+    y += __shfl_xor(y, 32);
+    const float res = valid ? y + b3 - T[j] : 0.f;
+    const float dy = 2.f * res / (float)batch;
+    if (g == 0) {
+      gb3 += dy;
+      loss += res * res;
+    }
+    // back: dz2, then dz1 = (W2 dz2) silu'(z1)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float4_t w3 = *reinterpret_cast<const float4_t*>(&sV[2][16 * t + 4 * g]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        gW3[t][r] += h[t][r] * dy;
+        z2[t][r] = dy * w3[r] * silu_grad_f(z2[t][r]);
+      }
+      gb2[t] += z2[t];
+      *reinterpret_cast<float4_t*>(&sB[(w * 16 + c) * PW + 16 * t + 4 * g]) = z2[t];
+    }
+    float4_t d[4] = {zero, zero, zero, zero};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float4_t a[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        a[t] = *reinterpret_cast<const float4_t*>(&sW2[(16 * t + c) * PW + 16 * k + 4 * g]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t][r], z2[k][r], d[t], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) d[t][r] *= silu_grad_f(z1[t][r]);
+      gb1[t] += d[t];
+    }
+    __syncthreads();
+    // dW2[i][n] += sum_s h1[s][i] dz2[s][n], rows i = 16w ..
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = (16 * k + 4 * g + r) * PW;
+        const float a = sA[row + 16 * w + c];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          gW2[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, sB[row + 16 * t + c], gW2[t], 0, 0, 0);
+      }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 4; ++t) *reinterpret_cast<float4_t*>(&sB[(w * 16 + c) * PW + 16 * t + 4 * g]) = d[t];
+    __syncthreads();
+    // dW1[q][i] += sum_s x[s][q] dz1[s][i], columns i = 16w ..
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * k + 4 * g + r;
+        const float b = sB[row * PW + 16 * w + c];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          gW1[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(sX[row * PX + 16 * t + c], b, gW1[t], 0, 0, 0);
+      }
+    __syncthreads();
   }
-  __syncthreads();
   float* out = partial + (int64_t)blockIdx.x * MLP_NPARAM_PAD;
-  // dW3, db3 (from h2 = silu(z2)) before z2 is overwritten by dz2
-  if (tid < HW) {
-    float g = 0.f;
-    for (int q = 0; q < TS; ++q) {
-      const float h = silu_f(sZ2[q][tid]);
-      g += (fp16 ? round_h(h) : h) * sdy[q];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[MLP_W2 + (16 * w + 4 * g + r) * HW + 16 * t + c] = gW2[t][r];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[MLP_W1 + (16 * t + 4 * g + r) * HW + 16 * w + c] = gW1[t][r];
+  // biases, W3 and the loss: over the 16 samples of a lane group, then over the wavefronts
+  auto sum16 = [](float v) {
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o);
+    return v;
+  };
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float v1 = sum16(gb1[t][r]), v2 = sum16(gb2[t][r]), v3 = sum16(gW3[t][r]);
+      if (c == 0) {
+        const int n = 16 * t + 4 * g + r;
+        sA[(0 * 4 + w) * HW + n] = v1;
+        sA[(1 * 4 + w) * HW + n] = v2;
+        sA[(2 * 4 + w) * HW + n] = v3;
+      }
     }
-    out[MLP_W3 + tid] = g;
-  }
-  if (tid == HW) {
-    float g = 0.f, L = 0.f;
-    for (int q = 0; q < TS; ++q) {
-      g += sdy[q];
-      L += sloss[q];
-    }
-    out[MLP_B3] = g;
-    out[MLP_NPARAM] = L;   // sum of squared residuals of this group
+  gb3 = sum16(gb3);
+  loss = sum16(loss);
+  if ((tid & 63) == 0) {
+    sB[w] = gb3;
+    sB[4 + w] = loss;
   }
   __syncthreads();
-  for (int c = 0; c < 16; ++c) {
-    const int n = n0 + c;
-    sZ2[s][n] = sdy[s] * sW3[n] * silu_grad_f(sZ2[s][n]);   // dz2
-  }
-  __syncthreads();
-  // dW2[i][n] = sum_s h1[s][i] dz2[s][n]; dz1 = (dz2 W2^T) * silu'(z1)
-  {
-    const int i = tid >> 2;
-    for (int c = 0; c < 16; ++c) {
-      const int n = n0 + c;
-      float g = 0.f;
-      for (int q = 0; q < TS; ++q) g += sH1[q][i] * sZ2[q][n];
-      out[MLP_W2 + i * HW + n] = g;
-    }
-  }
-  if (tid < HW) {
-    float g = 0.f;
-    for (int q = 0; q < TS; ++q) g += sZ2[q][tid];
-    out[MLP_B2 + tid] = g;
-  }
-  for (int c = 0; c < 16; ++c) {
-    const int i = n0 + c;
-    float d = 0.f;
-    for (int q = 0; q < HW; ++q) d += sZ2[s][q] * sW2[i * HW + q];
-    sZ1[s][i] = d * silu_grad_f(sZ1[s][i]);   // dz1 (own entries only)
-  }
-  __syncthreads();
-  // dW1[q][i] = sum_s x[s][q] dz1[s][i]
-  {
-    const int q = tid >> 3, i0 = (tid & 7) * 8;
-    for (int c = 0; c < 8; ++c) {
-      const int i = i0 + c;
-      float g = 0.f;
-      for (int r = 0; r < TS; ++r) g += sX[r][q] * sZ1[r][i];
-      out[MLP_W1 + q * HW + i] = g;
-    }
-  }
-  if (tid < HW) {
-    float g = 0.f;
-    for (int q = 0; q < TS; ++q) g += sZ1[q][tid];
-    out[MLP_B1 + tid] = g;
+  if (tid < 3 * HW) {
+    const int kind = tid >> 6, n = tid & 63;
+    const float* q = &sA[kind * 4 * HW + n];
+    out[(kind == 0 ? MLP_B1 : kind == 1 ? MLP_B2 : MLP_W3) + n] = (q[0] + q[HW]) + (q[2 * HW] + q[3 * HW]);
+  } else if (tid == 3 * HW) {
+    out[MLP_B3] = (sB[0] + sB[1]) + (sB[2] + sB[3]);
+    out[MLP_NPARAM] = (sB[4] + sB[5]) + (sB[6] + sB[7]);   // sum of squared residuals of this group
   }
 }
 
-// sum the partial gradients in block order; optionally apply Adam
-__global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ partial, int nblk,
+// Sums the partial gradients in a fixed order; optionally applies Adam. A
+// workgroup takes 64 parameters: 16 wavefronts sum every 16th partial each
+// (a thread per parameter walking all partials in turn waited for one load
+// after another, 250 us for 1024 partials; 5 us now for 512), then the first adds
+// the 16 sums in wavefront order.
+constexpr int RED_SLICES = 16;
+__global__ __launch_bounds__(64 * RED_SLICES) void k_mlp_reduce(const float* __restrict__ partial, int nblk,
                                                     float* __restrict__ grad, float* __restrict__ loss_sum,
                                                     float* __restrict__ P, _Float16* __restrict__ P16,
                                                     float* __restrict__ Mo, float* __restrict__ Vo, int adam,
                                                     float lr, float beta1, float beta2, float eps, float bc1,
                                                     float bc2) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p > MLP_NPARAM) return;
+  __shared__ float red[RED_SLICES][64];
+  const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
+  const int p = blockIdx.x * 64 + lane;
   float g = 0.f;
-  for (int b = 0; b < nblk; ++b) g += partial[(int64_t)b * MLP_NPARAM_PAD + p];
+  if (p <= MLP_NPARAM) {
+#pragma unroll 8
+    for (int b = slice; b < nblk; b += RED_SLICES) g += partial[(int64_t)b * MLP_NPARAM_PAD + p];
+  }
+  red[slice][lane] = g;
+  __syncthreads();
+  if (slice != 0 || p > MLP_NPARAM) return;
+#pragma unroll
+  for (int q = 1; q < RED_SLICES; ++q) g += red[q][lane];
   if (p == MLP_NPARAM) {
     *loss_sum = g;
     return;
@@ -651,17 +749,18 @@ void launch_mlp_forward(const ftcg_mlp_s* mlp, const float* feat, int64_t n, flo
 
 void launch_mlp_grad(ftcg_mlp_s* mlp, const float* X, const float* T, int64_t m, int64_t mb, int64_t nmb,
                      int64_t batch, int fp16, int adam, float lr, float* grad_out) {
-  const int nblk = (int)((batch + TS - 1) / TS);
+  const int64_t ntile = (batch + TS - 1) / TS;
+  const int nblk = (int)std::min<int64_t>(ntile, TG_MAX);
   mlp->partial.ensure(sizeof(float) * (size_t)nblk * MLP_NPARAM_PAD);
-  hipLaunchKernelGGL(k_mlp_grad, dim3(nblk), dim3(256), 0, mlp->stream, X, T, m, mb, nmb, batch,
-                     mlp->params.as<float>(), fp16, mlp->partial.as<float>());
+  hipLaunchKernelGGL(fp16 ? k_mlp_grad<true> : k_mlp_grad<false>, dim3(nblk), dim3(256), 0, mlp->stream, X, T, m, mb,
+                     nmb, batch, mlp->params.as<float>(), ntile, mlp->partial.as<float>());
   float bc1 = 1.f, bc2 = 1.f;
   if (adam) {
     mlp->step += 1;
     bc1 = 1.f - powf(mlp->beta1, (float)mlp->step);
     bc2 = 1.f - powf(mlp->beta2, (float)mlp->step);
   }
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((MLP_NPARAM + 1 + 255) / 256), dim3(256), 0, mlp->stream,
+  hipLaunchKernelGGL(k_mlp_reduce, dim3((MLP_NPARAM + 1 + 63) / 64), dim3(64 * RED_SLICES), 0, mlp->stream,
                      mlp->partial.as<float>(), nblk, grad_out ? grad_out : mlp->grad.as<float>(),
                      mlp->loss_dev.as<float>() + mlp->loss_slot, mlp->params.as<float>(),
                      mlp->params16.as<_Float16>(), mlp->adam_m.as<float>(), mlp->adam_v.as<float>(), adam, lr,
