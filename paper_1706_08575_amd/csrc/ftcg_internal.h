@@ -321,7 +321,8 @@ struct ftcg_plan_s {
   ftcg::DevBuf den_d;         // m complex: Omega^T Omega w
 
   // dense frame approximation (ftcg_frame_approx)
-  ftcg::DevBuf fa_gl, fa_G, fa_A, fa_diag, fa_beta, fa_tw, fa_tmp;
+  ftcg::DevBuf fa_gl, fa_G, fa_A, fa_diag, fa_beta, fa_tw, fa_tmp, fa_T;
+  bool fa_ready = false;      // fa_gl (quadrature) and fa_tw (mode-grid twiddles) are formed
 
   // learned weights
   struct ftcg_mlp_s* mlp = nullptr;
