@@ -356,7 +356,7 @@ ftcg_status ftcg_plan_create(ftcg_plan* out, int dim, const int64_t* n, int half
 ftcg_status ftcg_plan_destroy(ftcg_plan p) {
   if (!p) return FTCG_EINVAL;
   (void)hipStreamSynchronize(p->stream);
-  DevBuf* bufs[] = {&p->fa_gl, &p->fa_G, &p->fa_A, &p->fa_diag, &p->fa_beta, &p->fa_tw, &p->fa_tmp, &p->fa_T, &p->den_val, &p->den_d, &p->band_P, &p->band_col, &p->band_row, &p->band_c, &p->alpha,  &p->recs,  &p->alpha_s, &p->tile_cnt, &p->tile_off, &p->scan_tmp, &p->tile_scan_tmp, &p->check_part, &p->geo,
+  DevBuf* bufs[] = {&p->fa_gl, &p->fa_G, &p->fa_A, &p->fa_diag, &p->fa_beta, &p->fa_tw, &p->fa_tmp, &p->fa_T, &p->den_val, &p->den_d, &p->band_P, &p->band_col, &p->band_far, &p->band_c, &p->alpha,  &p->recs,  &p->alpha_s, &p->tile_cnt, &p->tile_off, &p->scan_tmp, &p->tile_scan_tmp, &p->check_part, &p->geo,
                     &p->flags,  &p->wb_cnt, &p->wb_off, &p->wb_rowoff, &p->wb_rowbuf, &p->ws_k,   &p->ws_idx,   &p->wb_of, &p->ws_inv, &p->ws_sum, &p->audit_buf,
                     &p->grid,   &p->fft_tmp, &p->deapod, &p->twiddle, &p->tile_order};
   for (DevBuf* b : bufs) b->release();

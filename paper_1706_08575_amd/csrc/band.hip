@@ -10,20 +10,19 @@
 //   (T_J^T T_J) c = T_J^T e_n = (T_{n,j})_{j in J(n)}.
 // Every entry of T_J^T T_J is an entry of the band of T^2 of half-width
 // 2r - 2: (T^2)_{a,b} for a, b in J(n). So:
-//   1. k_band_gram: P[a][e] = pi^(2 DIM) (T^2)_{a, a+e}, e = 0 .. 2r-2, one
-//      thread per sample a, walking a's neighbour bins once per pass of up
-//      to BAND_NC offsets e (each candidate i: T_ia and T_{i,a+e}; T_ia = 0
-//      outside a's box, so a's box is the whole sum);
+//   1. P[a][e] = pi^(2 DIM) (T^2)_{a, a+e}, e = 0 .. 2r-2. 2D: k_band_gram_mm,
+//      a wavefront per run of consecutive samples, the contraction over the
+//      candidates on the matrix cores; runs whose samples lie too far apart
+//      for that, and 1D: k_band_gram, one thread per sample a, walking
+//      a's neighbour bins once per pass of up to BAND_NC offsets e (each
+//      candidate i: T_ia and T_{i,a+e}; T_ia = 0 outside a's box, so a's box
+//      is the whole sum), every product rounded to a multiple of 2^-36
+//      (wq_product), so that its sums are exact in any order;
 //   2. k_band_solve: per column n, the (2r-1)^2 normal matrix gathered from
-//      P, the right-hand side from the pair terms of n, a float64 Cholesky
-//      factorisation in LDS (one thread per column, the matrix interleaved
-//      across the workgroup so consecutive threads hit consecutive banks),
-//      forward and back substitution; writes C by columns and by rows;
+//      P, the right-hand side from the pair terms of n, and a float64
+//      elimination over 16 lanes; writes C by columns;
 //   3. k_band_apply: c_i = sum_{|n - i| < r} C[i, n] fhat_n in float64, one
-//      thread per sample, from the row form (contiguous per i).
-// Like the diagonal weight sums, every product that enters a sum of step 1
-// is rounded to a multiple of 2^-36 (wq_product), so the sums are exact and
-// independent of the order of the samples within their bins.
+//      thread per sample, the columns of its neighbours through LDS.
 #include <algorithm>
 
 #include "ftcg_internal.h"
@@ -80,9 +79,12 @@ template <int DIM, int NC>
 __global__ __launch_bounds__(BAND_BLOCK) void k_band_gram(const WSample<DIM>* __restrict__ ss,
                                                          const int32_t* __restrict__ inv,
                                                          const int32_t* __restrict__ boff, int64_t m, WBinGeom g,
-                                                         int nband, int e0, double* __restrict__ P) {
+                                                         int nband, const int32_t* __restrict__ run_far, int stride,
+                                                         int* __restrict__ bad, double* __restrict__ P) {
   const int64_t a = (int64_t)blockIdx.x * BAND_BLOCK + threadIdx.x;
-  if (a >= m) return;
+  const int e0 = blockIdx.y * NC;
+  if (a == 0 && e0 == 0) *bad = 0;   // counted by the solve
+  if (a >= m || (run_far && !run_far[a / stride])) return;
   double x[DIM], sn[DIM], cs[DIM];
   load_sample<DIM>(ss[inv[a]], x, sn, cs);
   double cx[NC][DIM], csn[NC][DIM], ccs[NC][DIM], acc[NC];
@@ -116,93 +118,276 @@ __global__ __launch_bounds__(BAND_BLOCK) void k_band_gram(const WSample<DIM>* __
   }
 }
 
-template <class T>
-__global__ __launch_bounds__(BAND_BLOCK) void k_band_fill(T* __restrict__ p, int64_t n, T v) {
-  const int64_t i = (int64_t)blockIdx.x * BAND_BLOCK + threadIdx.x;
-  if (i < n) p[i] = v;
+// The band of T^2 of one run of consecutive samples per wavefront: samples
+// a0 .. a0 + 16 NBK - 1 in NBK blocks of 16, P[a][e] for the first `stride` of
+// them (a + e stays inside the blocks). Each step takes four candidates: lane (c, g)
+// forms T_{i,j} of candidate g with sample c of every block, which is the
+// operand layout of v_mfma_f64_16x16x4_f64 for both factors, and one
+// instruction per block adds T_ia T_ij over the four candidates for 16 x 16
+// pairs (a, j). So each T_{i,j} is formed once per run instead of once per sample
+// whose band holds it. The candidates are the bins around the run's
+// bounding box; a run that jumps by more than 2R between two samples (the end of a
+// pulse) is walked in parts, each with its own box and its samples alone as
+// the left factor. A run whose parts hold more bins than the samples' own
+// windows are worth (each sample's window once for its own terms, and about
+// half of it in the box for the band's; both counted in T terms) is left to
+// k_band_gram (run_far). Fixed order of addition. Float64 issue bounds it: at 512^2
+// with r = 8, 2^17 samples, 191 us against 687 us for one thread per
+// sample.
+typedef double double4_t __attribute__((ext_vector_type(4)));
+
+// numerator and denominator of band_term, and its box test; the shift of the
+// denominators is 2^-160 here, so that the product of three blocks' is normal
+// (2^-960 at least; the shift vanishes against any |k_i - k_n| above 2^-107)
+__device__ inline bool pair_parts(const WSample<2>& o, const double* x, const double* sn, const double* cs, double R,
+                                  double* num, double* den) {
+#pragma clang fp contract(off)
+  constexpr double EPS = 0x1p-160;
+  double nu = 1.0, de = 1.0, dmax = 0.0;
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const double d = o.k[a] - x[a];
+    dmax = a == 0 ? fabs(d) : fmax(dmax, fabs(d));
+    const double p1 = o.sc[a][0] * cs[a];
+    const double p2 = o.sc[a][1] * sn[a];
+    nu *= (p1 - p2) + EPS * WPI;
+    de *= d + EPS;
+  }
+  *num = nu;
+  *den = de;
+  return dmax <= R;
 }
 
-// One thread per column n. LDS: the packed lower triangle of the normal
-// matrix (NE = nb (nb + 1) / 2 entries) and the right-hand side (nb
-// entries), entry t of thread u at sm[t * blockDim + u].
-template <int DIM>
-__global__ void k_band_solve(const double* __restrict__ P, const WSample<DIM>* __restrict__ ss,
-                             const int32_t* __restrict__ inv, int64_t m, int r, double R,
-                             double* __restrict__ bcol, double* __restrict__ crow, int* __restrict__ bad) {
-  extern __shared__ double sm[];
-  const int nt = blockDim.x, u = threadIdx.x;
-  const int64_t n = (int64_t)blockIdx.x * nt + u;
-  if (n >= m) return;   // no barrier below: threads are independent
+// num / den of N pairs with one reciprocal, of the product of the denominators
+template <int N>
+__device__ inline void quotients(const double* num, const double* den, double* t) {
+  double pre[N];
+  pre[0] = den[0];
+#pragma unroll
+  for (int b = 1; b < N; ++b) pre[b] = pre[b - 1] * den[b];
+  double r = rcp64b(pre[N - 1]);
+#pragma unroll
+  for (int b = N - 1; b > 0; --b) {
+    t[b] = num[b] * (r * pre[b - 1]);
+    r *= den[b];
+  }
+  t[0] = num[0] * r;
+}
+
+template <int NBK>
+__global__ __launch_bounds__(BAND_BLOCK, NBK == 1 ? 8 : NBK == 2 ? 6 : 4) void k_band_gram_mm(const WSample<2>* __restrict__ ss,
+                                                            const int32_t* __restrict__ inv,
+                                                            const int32_t* __restrict__ boff, int64_t m, WBinGeom g,
+                                                            int nband, int stride, int32_t* __restrict__ run_far,
+                                                            double* __restrict__ P) {
+  const int lane = threadIdx.x & 63, c = lane & 15, q = lane >> 4;
+  const int64_t run = xcd_block(blockIdx.x, gridDim.x) * (BAND_BLOCK / 64) + (threadIdx.x >> 6);
+  const int64_t a0 = run * stride;
+  if (a0 >= m) return;   // no barrier below: wavefronts are independent
+  double x[NBK][2], sn[NBK][2], cs[NBK][2];
+  bool ok[NBK];
+#pragma unroll
+  for (int b = 0; b < NBK; ++b) {
+    const int64_t j = a0 + 16 * b + c;
+    ok[b] = j < m;
+    load_sample<2>(ss[inv[std::min<int64_t>(j, m - 1)]], x[b], sn[b], cs[b]);
+  }
+  int bin[2];
+  wbin_of<2>(x[0], g, bin);
+  const int na = (int)std::min<int64_t>(stride, m - a0);
+  const double px = __shfl(x[0][0], (lane - 1) & 63), py = __shfl(x[0][1], (lane - 1) & 63);
+  const bool brk = c < na && (c == 0 || fmax(fabs(x[0][0] - px), fabs(x[0][1] - py)) > 2.0 * g.R);
+  const unsigned starts = (unsigned)__ballot(brk) & 0xffffu;
+  // bins around the part of the run that starts at sample s: rows, columns
+  auto part = [&](int s, int e, int* lo, int* hi) {
+    const bool in = c >= s && c < e;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      int l = in ? bin[a] : 1 << 30, h = in ? bin[a] : -1;
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) {
+        l = min(l, __shfl_xor(l, o));
+        h = max(h, __shfl_xor(h, o));
+      }
+      lo[a] = __builtin_amdgcn_readfirstlane(max(l - g.span, 0));
+      hi[a] = __builtin_amdgcn_readfirstlane(min(h + g.span, g.nb[a] - 1));
+    }
+  };
+  auto next = [&](int s) {   // end of the part that starts at s
+    const unsigned later = starts & ~((2u << s) - 1u);
+    return later ? __ffs(later) - 1 : na;
+  };
+  int64_t cells = 0;
+  for (int s = 0; s < na;) {
+    const int e = next(s);
+    int lo[2], hi[2];
+    part(s, e, lo, hi);
+    cells += (int64_t)(hi[0] - lo[0] + 1) * (hi[1] - lo[1] + 1);
+    s = e;
+  }
+  const int w = 2 * g.span + 1;
+  const bool far = 2 * cells * 16 * NBK > (int64_t)na * w * w * (2 + nband);
+  if (lane == 0) run_far[run] = far;
+  if (far) return;
+  double4_t acc[NBK];
+#pragma unroll
+  for (int b = 0; b < NBK; ++b) acc[b] = (double4_t){0.0, 0.0, 0.0, 0.0};
+  for (int s = 0; s < na;) {
+    const int e = next(s);
+    const bool in = c >= s && c < e;
+    int lo[2], hi[2];
+    part(s, e, lo, hi);
+    for (int b0 = lo[0]; b0 <= hi[0]; ++b0) {
+      const int beg = boff[b0 * g.nb[1] + lo[1]], end = boff[b0 * g.nb[1] + hi[1] + 1];
+      for (int i0 = beg; i0 < end; i0 += 4) {
+        const int i = i0 + q;
+        const WSample<2> o = ss[min(i, end - 1)];
+        const double dx = o.k[0] - x[0][0], dy = o.k[1] - x[0][1];
+        const bool left = in && i < end && fmax(fabs(dx), fabs(dy)) <= g.R;
+        if (!__any(left)) continue;
+        double num[NBK], den[NBK], t[NBK];
+        bool box[NBK];
+#pragma unroll
+        for (int b = 0; b < NBK; ++b) box[b] = pair_parts(o, x[b], sn[b], cs[b], g.R, &num[b], &den[b]) && ok[b];
+        quotients<NBK>(num, den, t);
+        const double ta = left ? t[0] : 0.0;   // past the row's end and for other parts' samples: 0
+#pragma unroll
+        for (int b = 0; b < NBK; ++b)
+          acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ta, box[b] ? t[b] : 0.0, acc[b], 0, 0, 0);
+      }
+    }
+    s = e;
+  }
+#pragma unroll
+  for (int b = 0; b < NBK; ++b)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int a = 4 * v + q, e = 16 * b + c - a;   // accumulator v of lane (c, q): row 4v + q, column c
+      if (a < na && e >= 0 && e < nband && a0 + a + e < m) P[(a0 + a) * nband + e] = acc[b][v];
+    }
+}
+
+// element K of a row of 16 lanes, in every lane of the row
+template <int K>
+__device__ inline double row_bcast(double v) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x150 + K, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x150 + K, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+
+// Step K of the elimination: every other row loses its entry in column K
+// (columns K + 1 .. and the right-hand side are kept up to date). Row p is in
+// lane p % 16, set p / 16. ok clears when the pivot vanishes.
+template <int K, int NBP, int NS>
+__device__ inline void band_step(double (&A)[NS][NBP], double (&y)[NS], double (&ip)[NS], const double (&d0)[NS],
+                                 int c, bool& ok) {
+  constexpr int S = K / 16, KL = K % 16;
+  __builtin_amdgcn_sched_barrier(0);   // the next steps' broadcasts would not fit the registers
+  const double piv = row_bcast<KL>(A[S][K]);
+  ok = ok && piv > 1e-13 * row_bcast<KL>(d0[S]);
+  double r = rcp64b(piv);
+  r = fma(r, fma(-piv, r, 1.0), r);
+  double f[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const bool self = s == S && c == KL;
+    f[s] = self ? 0.0 : A[s][K] * r;
+    if (self) ip[s] = r;
+  }
+#pragma unroll
+  for (int t = K + 1; t < NBP; ++t) {
+    const double e = row_bcast<KL>(A[S][t]);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) A[s][t] = fma(-f[s], e, A[s][t]);
+  }
+  const double e = row_bcast<KL>(y[S]);
+#pragma unroll
+  for (int s = 0; s < NS; ++s) y[s] = fma(-f[s], e, y[s]);
+  if constexpr (K + 1 < NBP) band_step<K + 1, NBP, NS>(A, y, ip, d0, c, ok);
+}
+
+// Column n of C per group of 16 lanes: the L x L normal matrix of J(n), padded
+// to NBP with the identity, row p in the registers of lane p % 16 (set
+// p / 16), eliminated in place without a back substitution (in lockstep lanes
+// the rows above the pivot cost nothing extra). Pivots are the Cholesky
+// factorisation's (its squared diagonal); one vanishing against the
+// matrix's diagonal entry reports a column without full rank. Measured at 2^17
+// columns, r = 8: 51 us, against 241 us for one thread per column with the
+// triangle in LDS (69 KB per wavefront, two wavefronts per compute unit).
+template <int DIM, int NBP>
+__global__ __launch_bounds__(BAND_BLOCK) void k_band_solve(const double* __restrict__ P,
+                                                          const WSample<DIM>* __restrict__ ss,
+                                                          const int32_t* __restrict__ inv, int64_t m, int r, double R,
+                                                          double* __restrict__ bcol, int* __restrict__ bad) {
+  constexpr int NS = (NBP + 15) / 16;
+  const int c = threadIdx.x & 15;
+  const int64_t n = ((int64_t)blockIdx.x * BAND_BLOCK + threadIdx.x) >> 4;
+  if (n >= m) return;   // whole rows of lanes; no barrier below
   const int nb = 2 * r - 1;
-  const int NE = nb * (nb + 1) / 2;
   const int64_t lo = std::max<int64_t>(0, n - r + 1), hi = std::min<int64_t>(m - 1, n + r - 1);
   const int L = (int)(hi - lo + 1);
   const int off = (int)(lo - (n - r + 1));   // band position of J(n)'s first member
-  auto A = [&](int p, int q) -> double& { return sm[(int64_t)(p * (p + 1) / 2 + q) * nt + u]; };   // p >= q
-  auto Y = [&](int p) -> double& { return sm[(int64_t)(NE + p) * nt + u]; };
-  for (int p = 0; p < L; ++p)
-    for (int q = 0; q <= p; ++q) A(p, q) = P[(lo + q) * nb + (p - q)];
+  double A[NS][NBP], y[NS], ip[NS], d0[NS];
   double x[DIM], sn[DIM], cs[DIM];
   load_sample<DIM>(ss[inv[n]], x, sn, cs);
-  for (int p = 0; p < L; ++p) Y(p) = band_term<DIM>(ss[inv[lo + p]], x, sn, cs, R);
-  // Cholesky factorisation A = L L^T in place (lower triangle)
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int p = 16 * s + c;
+    const bool row = p < L;
+#pragma unroll
+    for (int t = 0; t < NBP; ++t) {
+      const bool on = row && t < L;
+      const double v = P[on ? (lo + min(p, t)) * nb + abs(p - t) : lo * nb];
+      A[s][t] = on ? v : (p == t ? 1.0 : 0.0);
+    }
+    d0[s] = row ? P[(lo + p) * nb] : 1.0;
+    y[s] = row ? band_term<DIM>(ss[inv[lo + p]], x, sn, cs, R) : 0.0;
+    ip[s] = 1.0;
+  }
   bool ok = true;
-  for (int p = 0; p < L && ok; ++p) {
-    double s = A(p, p);
-    for (int t = 0; t < p; ++t) s -= A(p, t) * A(p, t);
-    if (!(s > 1e-13 * A(p, p))) {
-      ok = false;
-      break;
-    }
-    const double d = sqrt(s), id = 1.0 / d;
-    A(p, p) = d;
-    for (int q = p + 1; q < L; ++q) {
-      double v = A(q, p);
-      for (int t = 0; t < p; ++t) v -= A(q, t) * A(p, t);
-      A(q, p) = v * id;
-    }
-  }
-  if (!ok) {
-    atomicAdd(bad, 1);
-    for (int p = 0; p < nb; ++p) bcol[n * nb + p] = 0.0;
-    return;
-  }
-  for (int p = 0; p < L; ++p) {   // L z = y
-    double v = Y(p);
-    for (int t = 0; t < p; ++t) v -= A(p, t) * Y(t);
-    Y(p) = v / A(p, p);
-  }
-  for (int p = L - 1; p >= 0; --p) {   // L^T x = z
-    double v = Y(p);
-    for (int t = p + 1; t < L; ++t) v -= A(t, p) * Y(t);
-    Y(p) = v / A(p, p);
-  }
+  band_step<0, NBP, NS>(A, y, ip, d0, c, ok);
+  if (!ok && c == 0) atomicAdd(bad, 1);
   // the sums carry pi^(2 DIM), the right-hand side pi^DIM: C = pi^DIM x
   constexpr double SC = DIM == 1 ? WPI : WPI * WPI;
-  for (int p = 0; p < nb; ++p) {
-    const int q = p - off;
-    const double c = (q >= 0 && q < L) ? SC * Y(q) : 0.0;
-    bcol[n * nb + p] = c;
-    // row i = n - r + 1 + p holds C[i, n] at e = n - i + r - 1 = 2 (r - 1) - p
-    if (q >= 0 && q < L) crow[(n - r + 1 + p) * nb + (2 * (r - 1) - p)] = c;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int p = 16 * s + c;
+    if (p < L) bcol[n * nb + off + p] = ok ? SC * (y[s] * ip[s]) : 0.0;
+    if (p < nb && (p < off || p >= off + L)) bcol[n * nb + p] = 0.0;
   }
 }
 
+// c_i: C[i, n] at [n][i - n + r - 1] of the column form. A workgroup's columns
+// are read once, in order, and each thread takes its anti-diagonal from
+// LDS (odd row length: no bank conflicts).
+constexpr int APPLY_NT = 128;
 template <class cx>
-__global__ __launch_bounds__(BAND_BLOCK) void k_band_apply(const double* __restrict__ crow,
-                                                          const cx* __restrict__ fhat, int64_t m, int r,
-                                                          cx* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * BAND_BLOCK + threadIdx.x;
+__global__ __launch_bounds__(APPLY_NT) void k_band_apply(const double* __restrict__ bcol,
+                                                        const cx* __restrict__ fhat, int64_t m, int r,
+                                                        cx* __restrict__ out) {
+  extern __shared__ double sc[];   // (APPLY_NT + 2 (r - 1)) x (2r - 1)
+  const int64_t i0 = (int64_t)blockIdx.x * APPLY_NT, i = i0 + threadIdx.x;
+  const int nb = 2 * r - 1, rows = APPLY_NT + 2 * (r - 1);
+  const int64_t first = (i0 - (r - 1)) * nb;
+#pragma unroll 4
+  for (int t = threadIdx.x; t < rows * nb; t += APPLY_NT) {
+    const int64_t at = first + t;
+    const bool on = at >= 0 && at < m * nb;
+    const double v = bcol[on ? at : 0];
+    sc[t] = on ? v : 0.0;
+  }
+  __syncthreads();
   if (i >= m) return;
-  const int nb = 2 * r - 1;
   double re = 0.0, im = 0.0;
+#pragma unroll 4
   for (int e = 0; e < nb; ++e) {
     const int64_t n = i + e - (r - 1);
-    if (n < 0 || n >= m) continue;
-    const double c = crow[i * nb + e];
-    const cx v = fhat[n];
-    re = fma(c, (double)v.x, re);
-    im = fma(c, (double)v.y, im);
+    const bool on = n >= 0 && n < m;
+    const double c = sc[(threadIdx.x + e) * nb + (nb - 1 - e)];
+    const cx v = fhat[on ? n : i];
+    re = fma(c, on ? (double)v.x : 0.0, re);
+    im = fma(c, on ? (double)v.y : 0.0, im);
   }
   cx o;
   o.x = (decltype(o.x))re;
@@ -210,12 +395,11 @@ __global__ __launch_bounds__(BAND_BLOCK) void k_band_apply(const double* __restr
   out[i] = o;
 }
 
-// threads per solve workgroup: the LDS of 64 columns when it fits 160 KiB
-static int solve_threads(int r) {
-  const int nb = 2 * r - 1;
-  const size_t per = (size_t)(nb * (nb + 1) / 2 + nb) * sizeof(double);
-  return per * 64 <= 160 * 1024 ? 64 : 32;
-}
+// samples per run of the matrix-core band: blocks of 16, and how many of the
+// first have their whole band inside them (one block up to r = 5, where 16 -
+// 2(r - 1) >= 8 samples per block still beat forming a second one; two up to r = 9)
+static int run_blocks(int r) { return r <= 5 ? 1 : r <= 9 ? 2 : 3; }
+static int run_stride(int r) { return std::min(16, 16 * run_blocks(r) - 2 * (r - 1)); }
 
 template <int DIM>
 static void launch_band(ftcg_plan p) {
@@ -225,29 +409,30 @@ static void launch_band(ftcg_plan p) {
   const WSample<DIM>* ss = p->ws_k.as<WSample<DIM>>();
   const int32_t* inv = p->ws_inv.as<int32_t>();
   const unsigned gb = (unsigned)((m + BAND_BLOCK - 1) / BAND_BLOCK);
+  const int32_t* boff = p->wb_off.as<int32_t>();
+  double* P = p->band_P.as<double>();
+  int* bad = reinterpret_cast<int*>(p->flags.as<double>() + 8);
   timing_begin(p, STEP_BAND_GRAM);
-  for (int e0 = 0; e0 < nb; e0 += BAND_NC)
-    hipLaunchKernelGGL((k_band_gram<DIM, BAND_NC>), dim3(gb), dim3(BAND_BLOCK), 0, s, ss, inv,
-                       p->wb_off.as<int32_t>(), m, p->wgeom, nb, e0, p->band_P.as<double>());
+  const int32_t* far = nullptr;
+  const int stride = run_stride(r);
+  if constexpr (DIM == 2) {
+    const int64_t runs = (m + stride - 1) / stride;
+    p->band_far.ensure(sizeof(int32_t) * runs);
+    const int nbk = run_blocks(r);
+    hipLaunchKernelGGL(nbk == 1 ? k_band_gram_mm<1> : nbk == 2 ? k_band_gram_mm<2> : k_band_gram_mm<3>,
+                       dim3((unsigned)((runs + BAND_BLOCK / 64 - 1) / (BAND_BLOCK / 64))), dim3(BAND_BLOCK), 0, s, ss,
+                       inv, boff, m, p->wgeom, nb, stride, p->band_far.as<int32_t>(), P);
+    far = p->band_far.as<int32_t>();
+  }
+  hipLaunchKernelGGL((k_band_gram<DIM, BAND_NC>), dim3(gb, (unsigned)((nb + BAND_NC - 1) / BAND_NC)), dim3(BAND_BLOCK),
+                     0, s, ss, inv, boff, m, p->wgeom, nb, far, stride, bad, P);
   FTCG_HIP(hipGetLastError());
   timing_end(p, STEP_BAND_GRAM);
   timing_begin(p, STEP_BAND_SOLVE);
-  const int64_t ne = m * nb;
-  hipLaunchKernelGGL(k_band_fill<double>, dim3((unsigned)((ne + BAND_BLOCK - 1) / BAND_BLOCK)), dim3(BAND_BLOCK), 0,
-                     s, p->band_row.as<double>(), ne, 0.0);
-  int* bad = reinterpret_cast<int*>(p->flags.as<double>() + 8);
-  hipLaunchKernelGGL(k_band_fill<int>, dim3(1), dim3(BAND_BLOCK), 0, s, bad, (int64_t)1, 0);
-  const int nt = solve_threads(r);
-  const size_t lds = (size_t)(nb * (nb + 1) / 2 + nb) * sizeof(double) * nt;
-  static bool attr_done[2] = {false, false};
-  if (!attr_done[DIM - 1]) {
-    FTCG_HIP(hipFuncSetAttribute((const void*)k_band_solve<DIM>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 160 * 1024));
-    attr_done[DIM - 1] = true;
-  }
-  hipLaunchKernelGGL(k_band_solve<DIM>, dim3((unsigned)((m + nt - 1) / nt)), dim3(nt), lds, s,
-                     p->band_P.as<double>(), ss, inv, m, r, p->R, p->band_col.as<double>(),
-                     p->band_row.as<double>(), bad);
+  const unsigned gs = (unsigned)((m * 16 + BAND_BLOCK - 1) / BAND_BLOCK);
+  hipLaunchKernelGGL((r <= 4 ? k_band_solve<DIM, 7> : r <= 8 ? k_band_solve<DIM, 15> : r <= 12 ? k_band_solve<DIM, 23>
+                                                                                     : k_band_solve<DIM, 31>),
+                     dim3(gs), dim3(BAND_BLOCK), 0, s, P, ss, inv, m, r, p->R, p->band_col.as<double>(), bad);
   FTCG_HIP(hipGetLastError());
   timing_end(p, STEP_BAND_SOLVE);
   // columns whose normal matrix is not positive definite (T[:, J(n)] without
@@ -265,7 +450,6 @@ void run_band_weights(ftcg_plan p) {
   const int nb = 2 * p->band_r - 1;
   p->band_P.ensure(sizeof(double) * m * nb);
   p->band_col.ensure(sizeof(double) * m * nb);
-  p->band_row.ensure(sizeof(double) * m * nb);
   p->band_c.ensure((p->dtype == FTCG_F64 ? 16 : 8) * (size_t)m);
   if (p->dim == 1)
     launch_band<1>(p);
@@ -274,14 +458,16 @@ void run_band_weights(ftcg_plan p) {
 }
 
 void band_apply(ftcg_plan p, const void* fhat) {
-  const unsigned gb = (unsigned)((p->m + BAND_BLOCK - 1) / BAND_BLOCK);
+  const unsigned gb = (unsigned)((p->m + APPLY_NT - 1) / APPLY_NT);
+  const int r = p->band_r;
+  const size_t lds = sizeof(double) * (APPLY_NT + 2 * (r - 1)) * (2 * r - 1);   // r <= 16: 39 KiB
   timing_begin(p, STEP_BAND_APPLY);
   if (p->dtype == FTCG_F64)
-    hipLaunchKernelGGL(k_band_apply<double2>, dim3(gb), dim3(BAND_BLOCK), 0, p->stream, p->band_row.as<double>(),
-                       static_cast<const double2*>(fhat), p->m, p->band_r, p->band_c.as<double2>());
+    hipLaunchKernelGGL(k_band_apply<double2>, dim3(gb), dim3(APPLY_NT), lds, p->stream, p->band_col.as<double>(),
+                       static_cast<const double2*>(fhat), p->m, r, p->band_c.as<double2>());
   else
-    hipLaunchKernelGGL(k_band_apply<float2>, dim3(gb), dim3(BAND_BLOCK), 0, p->stream, p->band_row.as<double>(),
-                       static_cast<const float2*>(fhat), p->m, p->band_r, p->band_c.as<float2>());
+    hipLaunchKernelGGL(k_band_apply<float2>, dim3(gb), dim3(APPLY_NT), lds, p->stream, p->band_col.as<double>(),
+                       static_cast<const float2*>(fhat), p->m, r, p->band_c.as<float2>());
   FTCG_HIP(hipGetLastError());
   timing_end(p, STEP_BAND_APPLY);
 }

@@ -311,8 +311,8 @@ struct ftcg_plan_s {
   int band_r = 1;             // band half-width r: 2r - 1 entries per column
   int band_bad = 0;           // columns whose normal equations broke down (last set_points)
   ftcg::DevBuf band_P;        // m x (2r-1): pi^(2 dim) (T^2)_{a, a+e}
-  ftcg::DevBuf band_col;      // m x (2r-1): C[n - r + 1 + p, n] (column form)
-  ftcg::DevBuf band_row;      // m x (2r-1): C[i, i + e - r + 1] (row form, for the apply)
+  ftcg::DevBuf band_col;      // m x (2r-1): C[n - r + 1 + p, n]
+  ftcg::DevBuf band_far;      // per run of samples: its band of T^2 is formed per sample (int32)
   ftcg::DevBuf band_c;        // m complex: C fhat of the last execute
 
   // iterative density compensation (FTCG_W_DENSITY)
