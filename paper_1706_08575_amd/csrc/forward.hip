@@ -14,9 +14,9 @@
 //      workgroup per square of ST x ST cells (S x S tiles of the spread's
 //      binning, ST = 32, or 64 for tiles of 64 in float32) stages that square's
 //      window of H (its ST + 2W - 1 rows and columns, indices modulo G) in
-//      LDS with coalesced loads, and walks the records of its tiles one per
-//      lane, keeping each sample's home record only (the record in the tile
-//      that holds its cell floor(u), so every sample is computed once): the
+//      LDS with coalesced loads, lists each sample's home record (the record in the tile
+//      that holds its cell floor(u), so every sample is computed once) in an
+//      order without LDS bank conflicts, and walks the list one record per lane: the
 //      lane forms the 2W column factors once, and for each row adds
 //      the row's taps against them (two fused multiply-adds and one LDS read
 //      per tap) before scaling the row sum by the row factor (rows by the
@@ -131,17 +131,72 @@ __device__ inline void gauss_taps(real f, real beta, real e2b, real (&out)[2 * W
 }
 
 
-template <class real, int W, int T, int ST>
+// What a square's kernel does with a sample's sum: the forward transform
+// stores it (FwdOut); a density iteration, whose grid is real, divides the
+// sample's weight by it (DenOut).
+template <class real>
+struct FwdOut {
+  using elem = typename CxI<real>::t;   // grid cells
+  static constexpr bool REAL = false;
+  elem* fhat;
+  __device__ void put(int src, real re, real im) const {
+    elem o;
+    o.x = re;
+    o.y = im;
+    fhat[src] = o;
+  }
+};
+template <class real>
+struct DenOut {
+  using elem = real;
+  static constexpr bool REAL = true;
+  double* w;
+  real* val;
+  double scale;
+  int last;
+  __device__ void put(int src, real re, real) const {
+    const double x = w[src] / (double)re;
+    w[src] = last ? x * scale : x;
+    if (!last) val[src] = (real)x;
+  }
+};
+
+// Order of a square's records. Every lane of a wavefront reads its taps at the
+// same offsets from its own first cell, so two lanes meet on an LDS bank in
+// all of their taps or in none, by their first cells modulo the banks' cells
+// (SLOTS). The home records of a chunk are listed round by round, a round taking
+// one record of every slot that has one left, in slot order: lanes that
+// are served together are on different banks, and no lane idles on another tile's
+// record. Positions come from each record's rank within its slot (an LDS
+// counter) and one ballot per round (records past SQ_ROUNDS of one slot
+// follow in any order); a sample's value does not depend on its
+// position. With records in binning order the kernel was bound by its LDS
+// reads, half of them conflicts, with 45 % of the lanes idle: 4096^2
+// raster, 2^23 samples, 605 against 530 us.
+constexpr int SQ_CHUNK = 512;   // records listed at a time: two per thread
+constexpr int SQ_ROUNDS = 32;
+
+template <class real, int W, int T, int ST, class OUT>
 __global__ __launch_bounds__(FWD_BLOCK) void k_interp2d_sq(const Rec<real>* __restrict__ recs,
                                                            const int32_t* __restrict__ tile_off,
-                                                           const typename CxI<real>::t* __restrict__ grid,
-                                                           int64_t G, int nt, real beta,
-                                                           typename CxI<real>::t* __restrict__ fhat) {
-  using cx = typename CxI<real>::t;
+                                                           const typename OUT::elem* __restrict__ grid,
+                                                           int64_t G, int nt, real beta, const OUT out) {
+  using elem = typename OUT::elem;
   constexpr int S = ST / T;             // tiles per edge of the square
   constexpr int L = 2 * W;
   constexpr int WS = ST + L - 1;        // window edge
-  __shared__ cx win[WS * WS];
+  constexpr int SLOTS = 256 / (int)sizeof(elem);   // cells across the 64 banks
+  constexpr int PER = SQ_CHUNK / FWD_BLOCK;
+  struct Item {
+    real f0, f1;
+    int cell, src;
+  };
+  __shared__ elem win[WS * WS];
+  __shared__ Item list[SQ_CHUNK];
+  __shared__ unsigned long long round_mask[SQ_ROUNDS];   // slots with a record in round q
+  __shared__ int round_base[SQ_ROUNDS];
+  __shared__ int cnt[SLOTS];
+  __shared__ int rest, total;           // first position past the rounds, records listed
   const int tid = threadIdx.x;
   const int nsq = nt / S;
   const int sq = (int)xcd_block(blockIdx.x, gridDim.x);
@@ -154,7 +209,6 @@ __global__ __launch_bounds__(FWD_BLOCK) void k_interp2d_sq(const Rec<real>* __re
     gc = gc < 0 ? gc + G : (gc >= G ? gc - G : gc);
     win[idx] = grid[gr * G + gc];
   }
-  __syncthreads();
   const real e2b = iexp((real)-2 * beta);
   for (int k = 0; k < S; ++k) {
     // the S tiles of this row of the square hold one contiguous record range
@@ -163,34 +217,87 @@ __global__ __launch_bounds__(FWD_BLOCK) void k_interp2d_sq(const Rec<real>* __re
     int bnd[S > 1 ? S - 1 : 1];
 #pragma unroll
     for (int q = 1; q < S; ++q) bnd[q - 1] = tile_off[id0 + q];
-    for (int r = rbeg + tid; r < rend; r += FWD_BLOCK) {
-      const Rec<real> rec = recs[r];
-      const int c0 = (int)(int16_t)(rec.c01 & 0xffff), c1 = rec.c01 >> 16;
-      if (c0 < 0 || c0 >= T || c1 < 0 || c1 >= T) continue;   // not the sample's home record
-      int q = 0;
+    for (int base = rbeg; base < rend; base += SQ_CHUNK) {
+      if (tid < SLOTS) cnt[tid] = 0;
+      __syncthreads();
+      Item it[PER];
+      int slot[PER], rank[PER];
 #pragma unroll
-      for (int m = 1; m < S; ++m) q += r >= bnd[m - 1];
-      real a[L], b[L];
-      gauss_taps<real, W>(rec.f0, beta, e2b, a);
-      gauss_taps<real, W>(rec.f1, beta, e2b, b);
-      const cx* p = win + (c0 + k * T) * WS + c1 + q * T;
-      real ar = 0, ai = 0;
-#pragma unroll 2   // two rows of reads in flight (all 2W rows would hold them all in registers)
-      for (int j = 0; j < L; ++j) {
-        real sr_ = 0, si_ = 0;
+      for (int u = 0; u < PER; ++u) {
+        const int r = base + u * FWD_BLOCK + tid;
+        slot[u] = -1;
+        rank[u] = 0;
+        if (r >= rend) continue;
+        const Rec<real> rec = recs[r];
+        const int c0 = (int)(int16_t)(rec.c01 & 0xffff), c1 = rec.c01 >> 16;
+        if (c0 < 0 || c0 >= T || c1 < 0 || c1 >= T) continue;   // not the sample's home record
+        int q = 0;
 #pragma unroll
-        for (int c = 0; c < L; ++c) {
-          const cx v = p[j * WS + c];
-          sr_ += b[c] * v.x;
-          si_ += b[c] * v.y;
-        }
-        ar += a[j] * sr_;
-        ai += a[j] * si_;
+        for (int m = 1; m < S; ++m) q += r >= bnd[m - 1];
+        it[u].f0 = rec.f0;
+        it[u].f1 = rec.f1;
+        it[u].src = rec.src;
+        it[u].cell = (c0 + k * T) * WS + c1 + q * T;
+        slot[u] = it[u].cell % SLOTS;
+        rank[u] = atomicAdd(&cnt[slot[u]], 1);
       }
-      cx o;
-      o.x = ar;
-      o.y = ai;
-      fhat[rec.src] = o;
+      __syncthreads();
+      if (tid < 64) {   // one wavefront: the rounds' slots and first positions
+        const int n = tid < SLOTS ? cnt[tid] : 0;
+        int at = 0, over = max(n - SQ_ROUNDS, 0);
+        for (int q = 0; q < SQ_ROUNDS; ++q) {
+          const unsigned long long mask = __ballot(n > q);
+          if (!mask) break;
+          if (tid == 0) {
+            round_base[q] = at;
+            round_mask[q] = mask;
+          }
+          at += __popcll(mask);
+        }
+        if (__any(over > 0)) {
+          for (int o = 32; o > 0; o >>= 1) over += __shfl_xor(over, o);
+        }
+        if (tid == 0) {
+          rest = at;
+          total = at + over;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < PER; ++u)
+        if (slot[u] >= 0) {
+          const int q = rank[u];
+          const int at = q < SQ_ROUNDS ? round_base[q] + __popcll(round_mask[q] & ((1ull << slot[u]) - 1ull))
+                                       : atomicAdd(&rest, 1);
+          list[at] = it[u];
+        }
+      const int n = total;
+      __syncthreads();
+      for (int r = tid; r < n; r += FWD_BLOCK) {
+        const Item rec = list[r];
+        real a[L], b[L];
+        gauss_taps<real, W>(rec.f0, beta, e2b, a);
+        gauss_taps<real, W>(rec.f1, beta, e2b, b);
+        const elem* p = win + rec.cell;
+        real ar = 0, ai = 0;
+#pragma unroll 2   // two rows of reads in flight (all 2W rows would hold them all in registers)
+        for (int j = 0; j < L; ++j) {
+          real sr_ = 0, si_ = 0;
+#pragma unroll
+          for (int c = 0; c < L; ++c) {
+            const elem v = p[j * WS + c];
+            if constexpr (OUT::REAL) {
+              sr_ += b[c] * v;
+            } else {
+              sr_ += b[c] * v.x;
+              si_ += b[c] * v.y;
+            }
+          }
+          ar += a[j] * sr_;
+          if constexpr (!OUT::REAL) ai += a[j] * si_;
+        }
+        out.put(rec.src, ar, ai);
+      }
     }
   }
 }
@@ -232,33 +339,53 @@ __global__ __launch_bounds__(FWD_BLOCK) void k_interp1d_tiles(const Rec<real>* _
   }
 }
 
-template <class real, int W, int ST>
-static void launch_interp_sq(ftcg_plan p, void* fhat) {
-  using cx = typename CxI<real>::t;
+template <class real, int W, int ST, class OUT>
+static void launch_interp_sq(ftcg_plan p, const OUT out) {
   const unsigned nsq = (unsigned)((p->G / ST) * (p->G / ST));
   const auto* k = p->recs.as<Rec<real>>();
   const auto* off = p->tile_off.as<int32_t>();
-  const auto* gr = p->grid.as<cx>();
-  auto* out = static_cast<cx*>(fhat);
+  const auto* gr = p->grid.as<typename OUT::elem>();
   const real beta = (real)p->beta;
   switch (p->tile) {
     case 16:
-      hipLaunchKernelGGL((k_interp2d_sq<real, W, 16, ST>), dim3(nsq), dim3(FWD_BLOCK), 0, p->stream, k, off, gr, p->G,
-                         (int)p->nt, beta, out);
+      hipLaunchKernelGGL((k_interp2d_sq<real, W, 16, ST, OUT>), dim3(nsq), dim3(FWD_BLOCK), 0, p->stream, k, off, gr,
+                         p->G, (int)p->nt, beta, out);
       break;
     case 32:
-      hipLaunchKernelGGL((k_interp2d_sq<real, W, 32, ST>), dim3(nsq), dim3(FWD_BLOCK), 0, p->stream, k, off, gr, p->G,
-                         (int)p->nt, beta, out);
+      hipLaunchKernelGGL((k_interp2d_sq<real, W, 32, ST, OUT>), dim3(nsq), dim3(FWD_BLOCK), 0, p->stream, k, off, gr,
+                         p->G, (int)p->nt, beta, out);
       break;
     default:
       if constexpr (ST == 64) {
-        hipLaunchKernelGGL((k_interp2d_sq<real, W, 64, ST>), dim3(nsq), dim3(FWD_BLOCK), 0, p->stream, k, off, gr,
+        hipLaunchKernelGGL((k_interp2d_sq<real, W, 64, ST, OUT>), dim3(nsq), dim3(FWD_BLOCK), 0, p->stream, k, off, gr,
                            p->G, (int)p->nt, beta, out);
         break;
       }
       throw StatusError{FTCG_EUNSUPPORTED};
   }
   FTCG_HIP(hipGetLastError());
+}
+
+// edge of the squares of a 2D plan's interpolation, 0 where its tiles are too
+// wide: 32 x 32 cells (64 for tile 64 in float32). Squares of 64 re-read fewer
+// window cells (1.37 instead of 1.81 per cell) but their 45 KiB windows leave
+// three workgroups per compute unit, and measured slower (4096^2 raster: 0.645
+// against 0.576 ms, before the records were listed)
+static int square_edge(const ftcg_plan_s* p) {
+  if (p->dtype == FTCG_F32 && p->tile == 64 && p->G % 64 == 0) return 64;
+  return p->tile <= 32 && p->G % 32 == 0 ? 32 : 0;
+}
+bool interp_in_squares(const ftcg_plan_s* p) { return p->dim == 2 && square_edge(p) > 0; }
+
+template <class real, int W, class OUT>
+static void launch_interp_squares(ftcg_plan p, const OUT out) {
+  if constexpr (sizeof(real) == 4) {
+    if (square_edge(p) == 64) {
+      launch_interp_sq<real, W, 64>(p, out);
+      return;
+    }
+  }
+  launch_interp_sq<real, W, 32>(p, out);
 }
 
 template <class real, int W>
@@ -270,20 +397,8 @@ static void launch_interp(ftcg_plan p, void* fhat) {
                        p->recs.as<Rec<real>>(), p->tile_off.as<int32_t>(), p->grid.as<cx>(), p->G, p->tile, beta,
                        static_cast<cx*>(fhat));
   } else {
-    // squares of 32 x 32 cells (64 for tile 64 in float32): squares of 64
-    // re-read fewer window cells (1.37 instead of 1.81 per cell) but their
-    // 45 KiB windows leave three workgroups per compute unit, and measured
-    // slower (4096^2 raster: 0.645 against 0.576 ms)
-    constexpr int STMAX = sizeof(real) == 4 ? 64 : 32;
-    const int T = p->tile;
-    if constexpr (STMAX == 64) {
-      if (T == 64 && p->G % 64 == 0) {
-        launch_interp_sq<real, W, 64>(p, fhat);
-        return;
-      }
-    }
-    if (T <= 32 && p->G % 32 == 0) {
-      launch_interp_sq<real, W, 32>(p, fhat);
+    if (interp_in_squares(p)) {
+      launch_interp_squares<real, W>(p, FwdOut<real>{static_cast<cx*>(fhat)});
       return;
     }
     // tiles of 128, or of 64 in float64: one workgroup per tile
@@ -322,6 +437,31 @@ void interpolate_grid(ftcg_plan p, void* out) {
     launch_interp_w<double>(p, out);
   else
     launch_interp_w<float>(p, out);
+}
+
+template <class real, int W>
+static void launch_interp_density(ftcg_plan p, double* w, void* val, double scale, bool last) {
+  launch_interp_squares<real, W>(p, DenOut<real>{w, static_cast<real*>(val), scale, last ? 1 : 0});
+}
+
+void interpolate_density(ftcg_plan p, double* w, void* val, double scale, bool last) {
+  auto go = [&](auto real_tag) {
+    using real = decltype(real_tag);
+    switch (p->W) {
+      case 2: launch_interp_density<real, 2>(p, w, val, scale, last); break;
+      case 3: launch_interp_density<real, 3>(p, w, val, scale, last); break;
+      case 4: launch_interp_density<real, 4>(p, w, val, scale, last); break;
+      case 5: launch_interp_density<real, 5>(p, w, val, scale, last); break;
+      case 6: launch_interp_density<real, 6>(p, w, val, scale, last); break;
+      case 7: launch_interp_density<real, 7>(p, w, val, scale, last); break;
+      case 8: launch_interp_density<real, 8>(p, w, val, scale, last); break;
+      default: throw StatusError{FTCG_EUNSUPPORTED};
+    }
+  };
+  if (p->dtype == FTCG_F64)
+    go(double{});
+  else
+    go(float{});
 }
 
 void forward_transform(ftcg_plan p, const void* image, void* fhat) {

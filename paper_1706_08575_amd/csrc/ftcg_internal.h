@@ -136,10 +136,13 @@ enum Accum { ACCUM_FIXED = 0, ACCUM_F64 = 1 };
 // quantum against its sign, which adds up over the thousands of taps a cell
 // of a dense tile receives) and packed as im * 2^32 + re in two's
 // complement, so that one 64-bit integer add accumulates both exactly.
+__device__ inline int fx_round(float x) {
+  int i;
+  asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(i) : "v"(x));
+  return i;
+}
 __device__ inline unsigned long long fx_pack(float pr, float pi) {
-  int ir, ii;
-  asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(ir) : "v"(pr));
-  asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(ii) : "v"(pi));
+  const int ir = fx_round(pr), ii = fx_round(pi);
   const unsigned hi = (unsigned)ii + (unsigned)(ir >> 31);
   return ((unsigned long long)hi << 32) | (unsigned)ir;
 }
@@ -398,6 +401,12 @@ void fft_cols_forward(bool f64, const void* in, int64_t in_stride, void* out, in
                       int64_t n, int cols, const double* dq, const double* drow, const void* tw, hipStream_t s);
 void forward_transform(ftcg_plan p, const void* image, void* fhat);   // type-2 transform at the plan's raster
 void interpolate_grid(ftcg_plan p, void* out);      // out_j = taps of sample j applied to p->grid
+// density iterations on real values and a real grid (2D)
+bool interp_in_squares(const ftcg_plan_s* p);
+bool density_real(const ftcg_plan_s* p);
+void spread_real(ftcg_plan p, const void* val, void* grid);
+// d_j from the real grid, then w_j <- w_j / d_j (times scale in the last iteration) and val_j = w_j
+void interpolate_density(ftcg_plan p, double* w, void* val, double scale, bool last);
 void run_density_weights(ftcg_plan p);              // iterative density compensation into p->alpha
 // dense frame approximation of the raster k (m samples) into image (float64 plans)
 void frame_approx(ftcg_plan p, int64_t m, const double* k, const void* fhat, void* image);
