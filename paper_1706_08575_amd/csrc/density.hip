@@ -6,7 +6,7 @@
 // The plan's spreading and interpolation kernels do the two products; the
 // weights live in float64 (the plan's alpha) and reach the spread as the
 // values (w, 0) in the plan's precision, in 2D as real values on a real
-// grid with the update in the interpolation (28 instead of 44 us per
+// grid with the update in the interpolation (27 instead of 44 us per
 // iteration at 512^2, 2^17 samples; the weights are the same bit for bit). The result is scaled by
 // (pi / (sigma beta))^dim, at which a uniform lattice of spacing h gets h^dim,
 // as the frame weights do.

@@ -22,6 +22,8 @@
 // XCDs round-robin) works on a contiguous range of rows; the 32-byte segments
 // of neighbouring blocks then meet in that XCD's L2 and leave it as whole
 // lines.
+#include <type_traits>
+
 #include "ftcg_internal.h"
 #include "batch_internal.h"
 
@@ -813,8 +815,15 @@ namespace ftcg {
 //   pass A: columns p1 of the image I[p0][p1]   -> T[p1][g0]  (n x G)
 //   pass B: columns g0 of T (positions p1)      -> H[g0][g1]  (G x G), the
 //           grid's own layout.
+//
+// DB (n = G / 2, two row buffers in LDS): the transform runs through
+// reg_ifft_db. The input of a column is then registers PPT / 4 .. 3 PPT / 4 - 1
+// of each thread, known at compile time, the others are zero, and the outputs
+// leave from the registers that the last stage ends in (4 LDS round trips and 4
+// barriers per 8192-point column instead of 6 and 12): 4096^2, both passes 525 ->
+// 457 us.
 // ---------------------------------------------------------------------------
-template <class real, int PPT, int RB>
+template <class real, int PPT, int RB, bool DB>
 __global__ void k_fft_cols_fwd(const typename CxF<real>::t* __restrict__ in, int64_t in_stride,
                                typename CxF<real>::t* __restrict__ out, int64_t out_row_stride, int L, int log2L,
                                int n, int crop_off, const double* __restrict__ dq, const double* __restrict__ drow,
@@ -822,7 +831,7 @@ __global__ void k_fft_cols_fwd(const typename CxF<real>::t* __restrict__ in, int
   using cx = typename CxF<real>::t;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx* buf = reinterpret_cast<cx*>(smem_raw);
-  cx* tw_lo = buf + padded_len(L);
+  cx* tw_lo = buf + (DB ? 2 : 1) * padded_len(L);
   cx* tw_hi = tw_lo + 64;
   const int ntw = 64 + max(1, (1 << log2T) >> 6);
   for (int i = threadIdx.x; i < ntw; i += blockDim.x) tw_lo[i] = tw[i];
@@ -831,6 +840,48 @@ __global__ void k_fft_cols_fwd(const typename CxF<real>::t* __restrict__ in, int
   double fc[RB];
 #pragma unroll
   for (int j = 0; j < RB; ++j) fc[j] = drow ? drow[r0 + j] : 1.0;
+  if constexpr (DB) {
+    constexpr int U0 = PPT / 4, NU = PPT / 2;   // position p = t + u nts is element crop_off + p = t + (U0 + u) nts
+    cx x[NU][RB];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int p = t + u * nts;
+      const cx* src = in + (int64_t)p * in_stride + r0;
+      double f = (p & 1) ? -1.0 : 1.0;          // crop_off is even
+      if (dq) f *= dq[p];
+#pragma unroll
+      for (int j = 0; j < RB; ++j) {
+        const cx v = src[j];
+        const real fs = (real)(f * fc[j]);
+        x[u][j].x = v.x * fs;
+        x[u][j].y = -v.y * fs;   // conjugate
+      }
+    }
+    int cur = 0;
+#pragma unroll
+    for (int j = 0; j < RB; ++j) {
+      cx v[PPT];
+#pragma unroll
+      for (int u = 0; u < PPT; ++u) {
+        if (u >= U0 && u < U0 + NU)
+          v[u] = x[u - U0][j];
+        else
+          v[u].x = v[u].y = (real)0;
+      }
+      reg_ifft_db<real, PPT>(v, buf, buf + padded_len(L), cur, L, log2L, t, nts, tw_lo, tw_hi, log2T);
+      cx* dst = out + (int64_t)(r0 + j) * out_row_stride;
+#pragma unroll
+      for (int u = 0; u < PPT; ++u) {
+        const int g = t + u * nts;
+        const real sg = (g & 1) ? (real)-1 : (real)1;
+        cx w;
+        w.x = v[u].x * sg;
+        w.y = v[u].y * -sg;      // conjugate
+        dst[g] = w;
+      }
+    }
+    return;
+  }
   // this thread's positions of all RB columns, scaled and conjugated: the
   // first column straight into the LDS row, the others held in registers
   cx x[PPT][RB > 1 ? RB - 1 : 1];
@@ -889,7 +940,7 @@ __global__ void k_fft_cols_fwd(const typename CxF<real>::t* __restrict__ in, int
   }
 }
 
-template <class real, int PPT, int RB>
+template <class real, int PPT, int RB, bool DB>
 static void launch_fwd_cols(const void* in, int64_t in_stride, void* out, int64_t out_row_stride, int64_t L,
                             int64_t n, int cols, const double* dq, const double* drow, const void* tw,
                             hipStream_t s) {
@@ -897,32 +948,56 @@ static void launch_fwd_cols(const void* in, int64_t in_stride, void* out, int64_
   int log2L = 0;
   while ((int64_t(1) << log2L) < L) ++log2L;
   const int nts = (int)std::max<int64_t>(64, L / PPT);
-  const size_t lds = ((size_t)padded_len((int)L) + 64 + std::max<int64_t>(1, L >> 6)) * sizeof(cx);
+  const size_t lds = ((DB ? 2 : 1) * (size_t)padded_len((int)L) + 64 + std::max<int64_t>(1, L >> 6)) * sizeof(cx);
   static bool attr_done = false;
   if (!attr_done) {
-    FTCG_HIP(hipFuncSetAttribute((const void*)k_fft_cols_fwd<real, PPT, RB>,
+    FTCG_HIP(hipFuncSetAttribute((const void*)k_fft_cols_fwd<real, PPT, RB, DB>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
     attr_done = true;
   }
-  hipLaunchKernelGGL((k_fft_cols_fwd<real, PPT, RB>), dim3((unsigned)(cols / RB)), dim3(nts), lds, s,
+  hipLaunchKernelGGL((k_fft_cols_fwd<real, PPT, RB, DB>), dim3((unsigned)(cols / RB)), dim3(nts), lds, s,
                      static_cast<const cx*>(in), in_stride, static_cast<cx*>(out), out_row_stride, (int)L, log2L,
                      (int)n, (int)((L - n) / 2), dq, drow, static_cast<const cx*>(tw), log2L);
   FTCG_HIP(hipGetLastError());
 }
 
+// the register path: 8 points per thread (L = 8 nts), the input the middle
+// half, and two padded rows and the twiddles within the 160 KiB of LDS
+template <class real, int PPT>
+static bool fwd_db(int64_t L, int64_t n) {
+  const int64_t lds = (2 * (int64_t)padded_len((int)L) + 64 + (L >> 6)) * 2 * (int64_t)sizeof(real);
+  return PPT == 8 && L >= 64 * PPT && 2 * n == L && lds <= 160 * 1024;
+}
+
 // RB columns per workgroup: 4 in float32 (32-byte read segments; the inputs
 // of the other three columns held in registers bring the kernel to the 128
 // VGPRs per lane of 1024-thread workgroups, with 2 spilled), else 1 (two
-// float64 columns spill 20 VGPRs; float32 rows of 16384 points take 16
+// float64 columns spill 20 VGPRs, except in the register path; float32 rows of 16384 points take 16
 // points per thread)
 template <class real, int PPT>
 static void fwd_cols_rb(const void* in, int64_t in_stride, void* out, int64_t out_row_stride, int64_t L, int64_t n,
                         int cols, const double* dq, const double* drow, const void* tw, hipStream_t s) {
   constexpr int RB = (PPT == 8 && sizeof(real) == 4) ? 4 : 1;
+  auto go = [&](auto kernel_rb, auto db) {
+    launch_fwd_cols<real, PPT, decltype(kernel_rb)::value, decltype(db)::value>(in, in_stride, out, out_row_stride, L, n,
+                                                                               cols, dq, drow, tw, s);
+  };
+  using One = std::integral_constant<int, 1>;
+  using Wide = std::integral_constant<int, RB>;
+  if constexpr (PPT == 8) {
+    if (fwd_db<real, PPT>(L, n)) {
+      using WideDb = std::integral_constant<int, sizeof(real) == 4 ? 4 : 2>;
+      if (cols % WideDb::value == 0)
+        go(WideDb{}, std::true_type{});
+      else
+        go(One{}, std::true_type{});
+      return;
+    }
+  }
   if (cols % RB == 0)
-    launch_fwd_cols<real, PPT, RB>(in, in_stride, out, out_row_stride, L, n, cols, dq, drow, tw, s);
+    go(Wide{}, std::false_type{});
   else
-    launch_fwd_cols<real, PPT, 1>(in, in_stride, out, out_row_stride, L, n, cols, dq, drow, tw, s);
+    go(One{}, std::false_type{});
 }
 
 // columns of n positions (column r at in[p in_stride + r]) -> zero-padded
