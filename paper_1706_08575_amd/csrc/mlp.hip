@@ -23,6 +23,8 @@
 // the partials in a fixed order and applies Adam to the float32 master
 // weights, refreshing their half copy.
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "ftcg_internal.h"
 #include "mlp_internal.h"
@@ -52,42 +54,140 @@ __device__ inline int wbin_clamp(double x, double kmin, double h, int nb) {
   return v < 0 ? 0 : (v >= nb ? nb - 1 : v);
 }
 
-__device__ inline void knn_visit(double kx0, double kx1, int oi, const double* x, int jself, double R,
-                                 unsigned long long (&key)[KNN]);
+// A key is the 64-bit word (float32 d2 bits << 32 | caller index) read as a
+// double: non-negative words below 0x7ff0... order as doubles as they do as
+// integers, so that a sorted insertion takes one v_min_f64 and one
+// v_max_f64 per slot (as integers it took a compare and four selects, about 100
+// instructions per accepted candidate). An empty slot is +infinity.
+#define KNN_EMPTY __builtin_inf()
 
-__device__ inline void knn_visit_bin(const WSample<2>* __restrict__ ss, const int32_t* __restrict__ sidx, int beg,
-                                     int end, const double* x, int jself, double R,
-                                     unsigned long long (&key)[KNN]) {
-  for (int i = beg; i < end; ++i) knn_visit(ss[i].k[0], ss[i].k[1], sidx[i], x, jself, R, key);
+// The keys are members, not an array, so that they are registers from the
+// first pass of the compiler on (as an array they became one 32-register
+// vector, copied whole at every branch).
+struct KnnKeys {
+  double k0, k1, k2, k3, k4, k5, k6, k7, k8, k9, k10, k11, k12, k13, k14, k15;
+  template <int Q>
+  __device__ double& at() {
+    if constexpr (Q == 0)
+      return k0;
+    else if constexpr (Q == 1)
+      return k1;
+    else if constexpr (Q == 2)
+      return k2;
+    else if constexpr (Q == 3)
+      return k3;
+    else if constexpr (Q == 4)
+      return k4;
+    else if constexpr (Q == 5)
+      return k5;
+    else if constexpr (Q == 6)
+      return k6;
+    else if constexpr (Q == 7)
+      return k7;
+    else if constexpr (Q == 8)
+      return k8;
+    else if constexpr (Q == 9)
+      return k9;
+    else if constexpr (Q == 10)
+      return k10;
+    else if constexpr (Q == 11)
+      return k11;
+    else if constexpr (Q == 12)
+      return k12;
+    else if constexpr (Q == 13)
+      return k13;
+    else if constexpr (Q == 14)
+      return k14;
+    else
+      return k15;
+  }
+};
+// f(constant 0), ..., f(constant KNN - 1)
+template <int... Q, class F>
+__device__ inline void each_key(std::integer_sequence<int, Q...>, F&& f) {
+  (f(std::integral_constant<int, Q>{}), ...);
+}
+template <class F>
+__device__ inline void each_key(F&& f) {
+  each_key(std::make_integer_sequence<int, KNN>{}, f);
+}
+
+// Inserts kc into the ascending keys, dropping the largest: key[q] becomes
+// min(key[q], max(key[q - 1], kc)), from the last down, in place. One asm
+// block, as the library's functions quiet their operands first (another
+// v_max_f64 each; no key is a NaN) and the compiler otherwise keeps both the old and the
+// new keys and copies them every time.
+__device__ inline void knn_insert(double kc, KnnKeys& key) {
+  static_assert(KNN == 16, "operands of the block");
+  double t;
+  asm(
+      "v_max_f64 %16, %14, %17\n"
+      "v_min_f64 %15, %15, %16\n"
+      "v_max_f64 %16, %13, %17\n"
+      "v_min_f64 %14, %14, %16\n"
+      "v_max_f64 %16, %12, %17\n"
+      "v_min_f64 %13, %13, %16\n"
+      "v_max_f64 %16, %11, %17\n"
+      "v_min_f64 %12, %12, %16\n"
+      "v_max_f64 %16, %10, %17\n"
+      "v_min_f64 %11, %11, %16\n"
+      "v_max_f64 %16, %9, %17\n"
+      "v_min_f64 %10, %10, %16\n"
+      "v_max_f64 %16, %8, %17\n"
+      "v_min_f64 %9, %9, %16\n"
+      "v_max_f64 %16, %7, %17\n"
+      "v_min_f64 %8, %8, %16\n"
+      "v_max_f64 %16, %6, %17\n"
+      "v_min_f64 %7, %7, %16\n"
+      "v_max_f64 %16, %5, %17\n"
+      "v_min_f64 %6, %6, %16\n"
+      "v_max_f64 %16, %4, %17\n"
+      "v_min_f64 %5, %5, %16\n"
+      "v_max_f64 %16, %3, %17\n"
+      "v_min_f64 %4, %4, %16\n"
+      "v_max_f64 %16, %2, %17\n"
+      "v_min_f64 %3, %3, %16\n"
+      "v_max_f64 %16, %1, %17\n"
+      "v_min_f64 %2, %2, %16\n"
+      "v_max_f64 %16, %0, %17\n"
+      "v_min_f64 %1, %1, %16\n"
+      "v_min_f64 %0, %0, %17"
+      : "+v"(key.k0), "+v"(key.k1), "+v"(key.k2), "+v"(key.k3), "+v"(key.k4),
+        "+v"(key.k5), "+v"(key.k6), "+v"(key.k7), "+v"(key.k8), "+v"(key.k9),
+        "+v"(key.k10), "+v"(key.k11), "+v"(key.k12), "+v"(key.k13), "+v"(key.k14), "+v"(key.k15), "=&v"(t)
+      : "v"(kc));
+}
+
+__device__ inline double knn_key(double dx, double dy, int oi) {
+  const float fx = (float)dx, fy = (float)dy;
+  const float d2 = __fadd_rn(__fmul_rn(fx, fx), __fmul_rn(fy, fy));
+  return __builtin_bit_cast(double, ((unsigned long long)__float_as_uint(d2) << 32) | (unsigned)oi);
+}
+__device__ inline float knn_d2(double key) {   // not of an empty slot
+  return __uint_as_float((unsigned)(__builtin_bit_cast(unsigned long long, key) >> 32));
 }
 
 // visits one candidate (caller index oi, coordinates kx) for sample (x, jself)
-__device__ inline void knn_visit(double kx0, double kx1, int oi, const double* x, int jself, double R,
-                                 unsigned long long (&key)[KNN]) {
+__device__ inline void knn_visit(double kx0, double kx1, int oi, const double* x, int jself, double R, KnnKeys& key) {
   const double dx = kx0 - x[0];
   const double dy = kx1 - x[1];
-  if (oi == jself || fabs(dx) > R || fabs(dy) > R) return;
-  const float fx = (float)dx, fy = (float)dy;
-  const float d2 = __fadd_rn(__fmul_rn(fx, fx), __fmul_rn(fy, fy));
-  const unsigned long long kc = ((unsigned long long)__float_as_uint(d2) << 32) | (unsigned)oi;
-  if (kc < key[KNN - 1]) {
-    // sorted insertion, branch free: walk down using the old neighbours
-#pragma unroll
-    for (int q = KNN - 1; q > 0; --q) {
-      const unsigned long long lo = key[q - 1];
-      key[q] = (kc < lo) ? lo : (kc < key[q] ? kc : key[q]);
-    }
-    key[0] = kc < key[0] ? kc : key[0];
-  }
+  const bool ok = (oi != jself) & (fmax(fabs(dx), fabs(dy)) <= R);
+  const double kc = knn_key(dx, dy, oi);
+  if (ok & (kc < key.k15)) knn_insert(kc, key);
+}
+
+__device__ inline void knn_visit_bin(const WSample<2>* __restrict__ ss, const int32_t* __restrict__ sidx, int beg,
+                                     int end, const double* x, int jself, double R, KnnKeys& key) {
+  for (int i = beg; i < end; ++i) knn_visit(ss[i].k[0], ss[i].k[1], sidx[i], x, jself, R, key);
 }
 
 // after the rings 0 .. r around bin (b0, b1): true when every unvisited
 // sample lies at least `reach` (the distance from x to the edge of the
 // (2r+1)^2 block, sides clipped at the bin grid's edge excluded) away and the
 // 16th key is strictly nearer than that (with a margin for float rounding)
-__device__ inline bool knn_done(const unsigned long long (&key)[KNN], const WBinGeom& g, const double* x, int b0,
+__device__ inline bool knn_done(KnnKeys& key, const WBinGeom& g, const double* x, int b0,
                                 int b1, int r) {
-  if (key[KNN - 1] == ~0ull) return false;
+  if (key.k15 == KNN_EMPTY) return false;
   const int lo0 = max(b0 - r, 0), hi0 = min(b0 + r, g.nb[0] - 1);
   const int lo1 = max(b1 - r, 0), hi1 = min(b1 + r, g.nb[1] - 1);
   double reach = 1e300;
@@ -95,15 +195,14 @@ __device__ inline bool knn_done(const unsigned long long (&key)[KNN], const WBin
   if (hi0 < g.nb[0] - 1) reach = fmin(reach, g.kmin[0] + (hi0 + 1) * g.h - x[0]);
   if (lo1 > 0) reach = fmin(reach, x[1] - (g.kmin[1] + lo1 * g.h));
   if (hi1 < g.nb[1] - 1) reach = fmin(reach, g.kmin[1] + (hi1 + 1) * g.h - x[1]);
-  const float d16 = __uint_as_float((unsigned)(key[KNN - 1] >> 32));
-  return (double)d16 < reach * reach * (1.0 - 1e-6);
+  return (double)knn_d2(key.k15) < reach * reach * (1.0 - 1e-6);
 }
 
 // rings r0 .. span around the sample's bin (b0, b1) from global memory, ring
 // by ring, until knn_done
 __device__ inline void knn_rings(const WSample<2>* __restrict__ ss, const int32_t* __restrict__ sidx,
                                  const int32_t* __restrict__ boff, const WBinGeom& g, const double* x, int jself,
-                                 int b0, int b1, int r0, unsigned long long (&key)[KNN]) {
+                                 int b0, int b1, int r0, KnnKeys& key) {
   for (int r = r0; r <= g.span; ++r) {
     const int lo0 = max(b0 - r, 0), hi0 = min(b0 + r, g.nb[0] - 1);
     const int lo1 = max(b1 - r, 0), hi1 = min(b1 + r, g.nb[1] - 1);
@@ -133,39 +232,51 @@ __device__ inline void knn_rings(const WSample<2>* __restrict__ ss, const int32_
 // unvisited sample is farther than the 16th (knn_done).
 __device__ inline void knn_search(const WSample<2>* __restrict__ ss, const int32_t* __restrict__ sidx,
                                   const int32_t* __restrict__ boff, const WBinGeom& g, const double* x, int jself,
-                                  unsigned long long (&key)[KNN]) {
-#pragma unroll
-  for (int q = 0; q < KNN; ++q) key[q] = ~0ull;
+                                  KnnKeys& key) {
+  each_key([&](auto q) { key.at<decltype(q)::value>() = KNN_EMPTY; });
   const int b0 = wbin_clamp(x[0], g.kmin[0], g.h, g.nb[0]);
   const int b1 = wbin_clamp(x[1], g.kmin[1], g.h, g.nb[1]);
   knn_rings(ss, sidx, boff, g, x, jself, b0, b1, 0, key);
 }
 
+// sin(pi (k_i - k_n)) from both samples' sines and cosines, exactly 0 for equal
+// coordinates: the products are rounded separately
+__device__ inline double sin_diff(double so, double co, double s, double c) {
+#pragma clang fp contract(off)
+  const double p1 = so * c, p2 = co * s;
+  return p1 - p2;
+}
+
 // features (float32) and the analytic estimate of one sample (sorted
 // position t) from its keys (caller indices, found in ss through inv)
-__device__ inline double knn_features_of(const unsigned long long (&key)[KNN], const WSample<2>* __restrict__ ss,
+__device__ inline double knn_features_of(KnnKeys& key, const WSample<2>* __restrict__ ss,
                                          const int32_t* __restrict__ inv, int64_t t, float R, float* f) {
   const double pi = 3.141592653589793238462643383279502884;
   const WSample<2> me = ss[t];
   const double x0 = me.k[0], x1 = me.k[1];
   const double s0 = me.sc[0][0], c0 = me.sc[0][1], s1 = me.sc[1][0], c1 = me.sc[1][1];
   double sum = 0.0;
-#pragma unroll
-  for (int q = 0; q < KNN; ++q) {
-    if (key[q] == ~0ull) {
-      f[2 * q] = R;
-      f[2 * q + 1] = R;
-      continue;
-    }
-    const WSample<2> o = ss[inv[(int64_t)(unsigned)(key[q] & 0xffffffffull)]];
+  constexpr double EPS = 0x1p-250;
+  each_key([&](auto c) {
+    constexpr int q = decltype(c)::value;
+    const double kk = key.at<q>();
+    const bool on = kk != KNN_EMPTY;
+    const unsigned j = on ? (unsigned)(__builtin_bit_cast(unsigned long long, kk) & 0xffffffffull) : 0u;
+    const WSample<2> o = ss[inv[j]];
     const double dx = o.k[0] - x0, dy = o.k[1] - x1;
-    f[2 * q] = (float)dx;
-    f[2 * q + 1] = (float)dy;
-    double g = 1.0;
-    if (dx != 0.0) g *= (o.sc[0][0] * c0 - o.sc[0][1] * s0) / (pi * dx);
-    if (dy != 0.0) g *= (o.sc[1][0] * c1 - o.sc[1][1] * s1) / (pi * dy);
-    sum += g * g;
-  }
+    f[2 * q] = on ? (float)dx : R;
+    f[2 * q + 1] = on ? (float)dy : R;
+    // pi^2 sinc(dx) sinc(dy) with one reciprocal, by the shifted quotients of the weight kernels
+    const double num = (sin_diff(o.sc[0][0], o.sc[0][1], s0, c0) + EPS * pi) *
+                       (sin_diff(o.sc[1][0], o.sc[1][1], s1, c1) + EPS * pi);
+    const double den = (dx + EPS) * (dy + EPS);
+    double r = __builtin_amdgcn_rcp(den);
+    r = fma(r, fma(-den, r, 1.0), r);
+    r = fma(r, fma(-den, r, 1.0), r);
+    const double g = num * r * (1.0 / (pi * pi));
+    sum += on ? g * g : 0.0;
+    if constexpr (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // four neighbours' loads in flight (all 16 spill)
+  });
   return 1.0 / (1.0 + sum);
 }
 
@@ -181,7 +292,7 @@ __global__ __launch_bounds__(256) void k_knn_features(const WSample<2>* __restri
   if (t >= m) return;
   const int j = sidx[t];
   const double x[2] = {ss[t].k[0], ss[t].k[1]};
-  unsigned long long key[KNN];
+  KnnKeys key;
   knn_search(ss, sidx, boff, g, x, j, key);
   float f[NF];
   const double b = knn_features_of(key, ss, inv, t, (float)g.R, f);
@@ -377,9 +488,8 @@ __global__ __launch_bounds__(256) void k_learned_weights(const WSample<2>* __res
       __syncthreads();
     }
   }
-  unsigned long long key[KNN];
-#pragma unroll
-  for (int q = 0; q < KNN; ++q) key[q] = ~0ull;
+  KnnKeys key;
+  each_key([&](auto q) { key.at<decltype(q)::value>() = KNN_EMPTY; });
   if (j >= 0) {
     if (staged) {
       // rings 0 .. KNN_RING from LDS, in the order and with the early exit
