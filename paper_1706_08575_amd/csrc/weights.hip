@@ -17,6 +17,8 @@
 // per-sample sin(pi k), cos(pi k), so each pair needs
 // sin(pi (k_i - k_n)) = sin(pi k_i) cos(pi k_n) - cos(pi k_i) sin(pi k_n)
 // instead of a transcendental, and one float64 reciprocal.
+#include <type_traits>
+
 #include "ftcg_internal.h"
 #include "wbins.h"
 
@@ -324,9 +326,17 @@ __global__ __launch_bounds__(WB_BLOCK) void k_frame_weights_rows(const WSample<2
 // 2^32 inside any window) and near 2^200 for an idle one (at 2^100), so the
 // product of two stays a normal number; d + eps == d for |d| >= 2^-196,
 // below which the factor is pi to rounding either way.
+// With SAME false the candidate lies in a later bin row, so its coordinate on
+// axis 0 is another number (the bin row is a function of it): that axis takes
+// no shift, and its sine difference is one product and one fused operation,
+// three of the pair's 28 or so float64 instructions less for the rows after
+// the first (about six of seven pairs). Measured, with the rows told apart against
+// one form for all: 133 against 146 us at 2^20 samples on 2048^2 (two samples
+// and two lanes), 292 against 321 on 1024^2 (two and four), 988 against 1065
+// at 2^19 on 256^2 (one and four).
 constexpr double WEPS_SYM = 0x1p-250;
 constexpr double WPI_EPS_SYM = WPI * WEPS_SYM;
-template <int WT>
+template <int WT, bool SAME>
 __device__ inline void sym_terms(const WSample<2>& o, const double (&x)[WT][2], const double (&sn)[WT][2],
                                  const double (&cs)[WT][2], double R, double (&q)[WT]) {
 #pragma clang fp contract(off)
@@ -339,10 +349,15 @@ __device__ inline void sym_terms(const WSample<2>& o, const double (&x)[WT][2], 
     in[u] = fmax(fabs(d0), fabs(d1)) <= R;
     // sin(pi (k_i - k_n)) = sin(pi k_i) cos(pi k_n) - cos(pi k_i) sin(pi k_n),
     // both products rounded, so it is exactly 0 when k_i == k_n
-    const double s0 = o.sc[0][0] * cs[u][0] - o.sc[0][1] * sn[u][0];
     const double s1 = o.sc[1][0] * cs[u][1] - o.sc[1][1] * sn[u][1];
-    num[u] = (s0 + WPI_EPS_SYM) * (s1 + WPI_EPS_SYM);
-    den[u] = (d0 + WEPS_SYM) * (d1 + WEPS_SYM);
+    if constexpr (SAME) {
+      const double s0 = o.sc[0][0] * cs[u][0] - o.sc[0][1] * sn[u][0];
+      num[u] = (s0 + WPI_EPS_SYM) * (s1 + WPI_EPS_SYM);
+      den[u] = (d0 + WEPS_SYM) * (d1 + WEPS_SYM);
+    } else {
+      num[u] = fma(o.sc[0][0], cs[u][0], -(o.sc[0][1] * sn[u][0])) * (s1 + WPI_EPS_SYM);
+      den[u] = d0 * (d1 + WEPS_SYM);
+    }
   }
   if constexpr (WT == 1) {
     q[0] = num[0] * rcp64(den[0]);
@@ -370,12 +385,12 @@ __device__ inline void sym_terms(const WSample<2>& o, const double (&x)[WT][2], 
 // the lane's samples); adding the 0 instead keeps the loop one basic block,
 // which pays where a wavefront's lanes walk long ranges (two lanes per
 // group), and not with four.
-template <int WT, bool SKIP0>
+template <int WT, bool SKIP0, bool SAME>
 __device__ inline void sym_pair(double (&acc)[WT], double* cacc, int p, const WSample<2>& o,
                                 const double (&x)[WT][2], const double (&sn)[WT][2], const double (&cs)[WT][2],
                                 double R) {
   double q[WT];
-  sym_terms<WT>(o, x, sn, cs, R, q);
+  sym_terms<WT, SAME>(o, x, sn, cs, R, q);
   double c = WQ_MAGIC;
 #pragma unroll
   for (int u = 0; u < WT; ++u) {
@@ -576,10 +591,16 @@ __global__ __launch_bounds__(WB_BLOCK, 5) void k_frame_weights_sym(const WSample
         if (len > 0) {
           const unsigned ph = ((unsigned)((t0 / WT) * S + sub) - (unsigned)a0) & 15u;
           int p = a0 + (int)(ph % (unsigned)len);
-          for (int j = 0; j < len; ++j) {
-            sym_pair<WT, (S > 2)>(acc, cacc, p, ld_wsample(cand_at(cand, p)), x, sn, cs, g.R);
-            p = p + 1 == a1 ? a0 : p + 1;
-          }
+          auto walk = [&](auto same) {
+            for (int j = 0; j < len; ++j) {
+              sym_pair<WT, (S > 2), decltype(same)::value>(acc, cacc, p, ld_wsample(cand_at(cand, p)), x, sn, cs, g.R);
+              p = p + 1 == a1 ? a0 : p + 1;
+            }
+          };
+          if (r == b0)
+            walk(std::true_type{});
+          else
+            walk(std::false_type{});
         }
         __syncthreads();
         for (int i = threadIdx.x; i < q1 - q0; i += WB_BLOCK) {
