@@ -102,7 +102,12 @@ __global__ __launch_bounds__(BATCH_BLOCK) void k_spread_persistent(const BatchTa
   constexpr int ROWS = T + 2 * PAD;
   constexpr int RPW = 64 / L;
   constexpr int NWAVES = BATCH_BLOCK / 64;
+  // records staged as in the single-plan kernel, while they fit 64 KiB with the tile
+  constexpr bool STAGED = ROWS * TP * 8 + FX_STAGE * 24 <= 64 * 1024;
+  constexpr int STG = STAGED ? FX_STAGE : 1;
   __shared__ unsigned long long acc[ROWS * TP];
+  __shared__ float4 sgeo[STG];   // f1, first row's kernel value, ratio of the rows, c01 (bits)
+  __shared__ float2 sval[STG];   // alpha * fhat
   __shared__ int task_sh;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int s = lane / L, i = lane - (lane / L) * L;
@@ -135,29 +140,45 @@ __global__ __launch_bounds__(BATCH_BLOCK) void k_spread_persistent(const BatchTa
     const float2* fhat = args->fhat + it.fhat_off;
     for (int idx = tid; idx < ROWS * TP; idx += BATCH_BLOCK) acc[idx] = 0ull;
     __syncthreads();
-    for (int base = tk.beg + wave * RPW; base < tk.end; base += NWAVES * RPW) {
-      const int r = base + s;
-      if (s < RPW && r < tk.end) {
-        const Rec<float> rec = it.recs[r];
-        const int c1 = rec.c01 >> 16;
-        const int col = c1 - W + 1 + i;
-        if (col >= 0 && col < T) {
-          const float a = it.alpha_s[r] * scale;
-          const float2 v = fhat[rec.src];
-          const int c0 = (int)(int16_t)(rec.c01 & 0xffff);
-          const float d1 = (float)(i - W + 1) - rec.f1;
-          const float d0 = (float)(1 - W) - rec.f0;
-          const float w10 = __expf(-beta * (d1 * d1 + d0 * d0)) * a;
-          float q = __expf(-beta * (2.f * d0 + 1.f));
-          float pr = v.x * w10, pi = v.y * w10;
-          unsigned long long* dst = acc + (c0 - W + 1 + PAD) * TP + col;
-#pragma unroll
-          for (int j = 0; j < L; ++j) {
-            __hip_atomic_fetch_add(dst + j * TP, fx_pack(pr, pi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            pr *= q;
-            pi *= q;
-            q *= e2b;
-          }
+    // one record's 2W x 2W taps: lane i takes footprint column i
+    auto splat = [&](float4 geo, float2 v) {
+      const int c01 = __float_as_int(geo.w);
+      const int col = (c01 >> 16) - W + 1 + i;
+      if (col < 0 || col >= T) return;
+      const int c0 = (int)(int16_t)(c01 & 0xffff);
+      const float w = fx_first((float)(i - W + 1) - geo.x, beta, geo.y, scale);
+      fx_column<L>(acc + (c0 - W + 1 + PAD) * TP + col, TP, v.x * w, v.y * w, geo.z, e2b);
+    };
+    auto record = [&](int r, float4& geo, float2& v) {
+      const Rec<float> rec = it.recs[r];
+      const float a = it.alpha_s[r];
+      const float2 f = fhat[rec.src];
+      const float d0 = (float)(1 - W) - rec.f0;
+      geo = make_float4(rec.f1, fx_row0(d0, beta), fx_ratio(d0, beta), __int_as_float(rec.c01));
+      v = make_float2(f.x * a, f.y * a);
+    };
+    if constexpr (STAGED) {
+      for (int cb = tk.beg; cb < tk.end; cb += FX_STAGE) {
+        const int cn = min(tk.end - cb, FX_STAGE);
+        if (cb != tk.beg) __syncthreads();   // every wavefront has left the previous chunk
+        for (int r = tid; r < cn; r += BATCH_BLOCK) {
+          float4 geo;
+          float2 v;
+          record(cb + r, geo, v);
+          sgeo[r] = geo;
+          sval[r] = v;
+        }
+        __syncthreads();
+        fx_pass<RPW, NWAVES>(sgeo, sval, cn, wave, s, splat);
+      }
+    } else {
+      for (int base = tk.beg + wave * RPW; base < tk.end; base += NWAVES * RPW) {
+        const int r = base + s;
+        if (s < RPW && r < tk.end) {
+          float4 geo;
+          float2 v;
+          record(r, geo, v);
+          splat(geo, v);
         }
       }
     }

@@ -169,14 +169,6 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d(const Rec<real>* __re
 // flush); columns outside the tile are skipped per lane.
 // ---------------------------------------------------------------------------
 
-// Records are staged in LDS in chunks of FX_STAGE (the first chunk while the
-// bound is formed): each record's geometry, weight and sample value are read
-// from global memory by one thread, in parallel over the workgroup, and the
-// tap loop then reads LDS only, so the dependent record -> sample loads are
-// not paid once per record batch of each wavefront (4096^2 SAS raster, 8.4M
-// samples: 0.73 -> 0.59 ms; on small grids the LDS atomics bound the loop).
-constexpr int FX_STAGE = 256;   // 6 KiB: keeps 7 workgroups of tile 32, W = 6 per CU
-
 // SRC: FX_RECS, record r has weight alpha_s[r]; FX_SUMS, the records carry no
 // weights yet, and record r of sample j takes alpha_j = pi^2 pi^2 / wsum[inv[j]]
 // (bin-order sums of the symmetric weight kernel, the same float64 division
@@ -184,7 +176,7 @@ constexpr int FX_STAGE = 256;   // 6 KiB: keeps 7 workgroups of tile 32, W = 6 p
 // a real grid (the density iterations): the cells are the low words of the
 // packed ones, added with 32-bit LDS atomics (14.5 instead of 9.9 lanes per
 // clock, and no packing), the sums bit for bit the real parts of the complex form.
-// 512^2 raster, 2^17 samples: 16.0 against 21.8 us.
+// 512^2 raster, 2^17 samples: 15.2 against 20.9 us.
 enum FxSrc { FX_RECS = 0, FX_SUMS = 1, FX_REAL = 2 };
 template <int SRC>
 struct FxTypes {
@@ -216,16 +208,29 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
     else
       return alpha_s[r];
   };
-  // the larger |component| of a value times its weight; NaN and infinities give infinity
-  auto size_of = [](val_t v, float a) -> float {
+  // a record's weighted value
+  auto value = [&](int r, int src) -> val_t {
+    const val_t v = fhat[src];
+    const float a = weight(r, src);
+    if constexpr (REAL)
+      return v * a;
+    else
+      return make_float2(v.x * a, v.y * a);
+  };
+  // its larger |component|; NaN and infinities give infinity
+  auto size_of = [](val_t v) -> float {
     float m, t;
     if constexpr (REAL) {
-      m = t = fabsf(v * a);
+      m = t = fabsf(v);
     } else {
-      m = fabsf(v.x * a);
-      t = fabsf(v.y * a);
+      m = fabsf(v.x);
+      t = fabsf(v.y);
     }
     return (isfinite(m) && isfinite(t)) ? fmaxf(m, t) : __builtin_inff();
+  };
+  auto geometry = [&](const Rec<float>& rec) -> float4 {
+    const float d0 = (float)(1 - W) - rec.f0;
+    return make_float4(rec.f1, fx_row0(d0, beta), fx_ratio(d0, beta), __int_as_float(rec.c01));
   };
   constexpr int L = 2 * W;              // lanes per record / taps per axis
   constexpr int PAD = 2 * W - 1;        // halo rows each side
@@ -235,8 +240,8 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
   constexpr bool STAGED = ROWS * TP * 8 + FX_STAGE * 24 <= 64 * 1024;
   constexpr int STG = STAGED ? FX_STAGE : 1;
   __shared__ cell_t acc[ROWS * TP];
-  __shared__ float4 sgeo[STG];          // f0, f1, c01 (bits), alpha
-  __shared__ val_t sval[STG];           // fhat[src]
+  __shared__ float4 sgeo[STG];          // f1, first row's kernel value, ratio of the rows, c01 (bits)
+  __shared__ val_t sval[STG];           // alpha * fhat[src]
   __shared__ float red[SPREAD_BLOCK / 64];
   __shared__ long long red2[SPREAD_BLOCK / 64];
 
@@ -259,13 +264,12 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
   float mx = 0.f;
   for (int r = beg + tid; r < end; r += SPREAD_BLOCK) {
     const Rec<float> rec = recs[r];
-    const float a = weight(r, rec.src);
-    const val_t v = fhat[rec.src];
+    const val_t v = value(r, rec.src);
     if (r - beg < first) {
-      sgeo[r - beg] = make_float4(rec.f0, rec.f1, __int_as_float(rec.c01), a);
+      sgeo[r - beg] = geometry(rec);
       sval[r - beg] = v;
     }
-    mx = fmaxf(mx, size_of(v, a));
+    mx = fmaxf(mx, size_of(v));
   }
   for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
   if (lane == 0) red[wave] = mx;
@@ -288,17 +292,12 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
   const float qs = 1048576.f / mx;
   long long qsum = 0;
   for (int r = beg + tid; r < end; r += SPREAD_BLOCK) {
-    float a;
     val_t v;
-    if (r - beg < first) {   // staged by this thread in the first pass
-      a = sgeo[r - beg].w;
+    if (r - beg < first)   // staged by this thread in the first pass
       v = sval[r - beg];
-    } else {
-      const int src = recs[r].src;
-      a = weight(r, src);
-      v = fhat[src];
-    }
-    qsum += (long long)ceilf(size_of(v, a) * qs) + 1;
+    else
+      v = value(r, recs[r].src);
+    qsum += (long long)ceilf(size_of(v) * qs) + 1;
   }
   for (int off = 32; off > 0; off >>= 1) qsum += __shfl_xor(qsum, off);
   __syncthreads();
@@ -315,35 +314,17 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
   const float e2b = __expf(-2.f * beta);
   constexpr int NWAVES = SPREAD_BLOCK / 64;
   // one record's 2W x 2W taps: lane i takes footprint column i
-  auto splat = [&](float f0, float f1, int c01, float araw, val_t v) {
-    const int c1 = c01 >> 16;
-    const int col = c1 - W + 1 + i;
+  auto splat = [&](float4 geo, val_t v) {
+    const int c01 = __float_as_int(geo.w);
+    const int col = (c01 >> 16) - W + 1 + i;
     if (col < 0 || col >= T) return;
-    const float a = araw * scale;
     const int c0 = (int)(int16_t)(c01 & 0xffff);
-    const float d1 = (float)(i - W + 1) - f1;
-    const float d0 = (float)(1 - W) - f0;
-    const float w10 = __expf(-beta * (d1 * d1 + d0 * d0)) * a;
-    float q = __expf(-beta * (2.f * d0 + 1.f));
+    const float w = fx_first((float)(i - W + 1) - geo.x, beta, geo.y, scale);
     cell_t* dst = acc + (c0 - W + 1 + PAD) * TP + col;
-    if constexpr (REAL) {
-      float pr = v * w10;
-#pragma unroll
-      for (int j = 0; j < L; ++j) {
-        __hip_atomic_fetch_add(dst + j * TP, (unsigned)fx_round(pr), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        pr *= q;
-        q *= e2b;
-      }
-    } else {
-      float pr = v.x * w10, pi = v.y * w10;
-#pragma unroll
-      for (int j = 0; j < L; ++j) {
-        __hip_atomic_fetch_add(dst + j * TP, fx_pack(pr, pi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        pr *= q;
-        pi *= q;
-        q *= e2b;
-      }
-    }
+    if constexpr (REAL)
+      fx_column<L>(dst, TP, v * w, geo.z, e2b);
+    else
+      fx_column<L>(dst, TP, v.x * w, v.y * w, geo.z, e2b);
   };
   if constexpr (STAGED) {
     for (int cb = beg; cb < end; cb += FX_STAGE) {
@@ -352,29 +333,19 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
         __syncthreads();
         for (int r = tid; r < cn; r += SPREAD_BLOCK) {
           const Rec<float> rec = recs[cb + r];
-          sgeo[r] = make_float4(rec.f0, rec.f1, __int_as_float(rec.c01), weight(cb + r, rec.src));
-          sval[r] = fhat[rec.src];
+          sgeo[r] = geometry(rec);
+          sval[r] = value(cb + r, rec.src);
         }
         __syncthreads();
       }
-      // the RPW records of one pass are cn / RPW apart in the chunk: records
-      // next to each other come from neighbouring samples of one pulse, whose
-      // footprints overlap, and in one pass they would meet on the same LDS banks
-      const int np = (cn + RPW - 1) / RPW;
-      for (int pass = wave; pass < np; pass += NWAVES) {
-        const int r = s * np + pass;
-        if (s < RPW && r < cn) {
-          const float4 g4 = sgeo[r];
-          splat(g4.x, g4.y, __float_as_int(g4.z), g4.w, sval[r]);
-        }
-      }
+      fx_pass<RPW, NWAVES>(sgeo, sval, cn, wave, s, splat);
     }
   } else {
     for (int base = beg + wave * RPW; base < end; base += NWAVES * RPW) {
       const int r = base + s;
       if (s < RPW && r < end) {
         const Rec<float> rec = recs[r];
-        splat(rec.f0, rec.f1, rec.c01, weight(r, rec.src), fhat[rec.src]);
+        splat(geometry(rec), value(r, rec.src));
       }
     }
   }
@@ -446,8 +417,8 @@ __global__ __launch_bounds__(SEG_BLOCK) void k_spread2d_seg(const Rec<float>* __
   constexpr int TP = SEG_COLS + 1;      // row pitch (64-bit words)
   __shared__ unsigned long long acc[ROWS * TP];
   __shared__ float2 carry[CROWS * SEG_COLS];
-  __shared__ float2 sf[SEG_BLOCK];      // f0, f1
-  __shared__ int sc[SEG_BLOCK];         // LDS row | LDS column << 16 of the record's first tap
+  __shared__ float4 sgeo[SEG_BLOCK];    // f1, first kept row's kernel value, ratio of the rows, and (bits)
+                                        // LDS row | LDS column << 16 of the record's first tap
   __shared__ float2 sv[SEG_BLOCK];      // alpha * fhat
   __shared__ float red[SEG_BLOCK / 64];
   __shared__ long long red2[SEG_BLOCK / 64];
@@ -504,8 +475,9 @@ __global__ __launch_bounds__(SEG_BLOCK) void k_spread2d_seg(const Rec<float>* __
       const unsigned long long mine = clip ? bc : bh;
       const int rank = __popcll(mine & ((1ull << lane) - 1ull));
       const int slot = clip ? SEG_BLOCK - 1 - (basec + rank) : baseh + rank;
-      sf[slot] = make_float2(f0, f1);
-      sc[slot] = packed;
+      const int j0 = max(0, -(int)(int16_t)(packed & 0xffff));   // 0 but for a clipped record
+      const float d0 = (float)(1 - W + j0) - f0;
+      sgeo[slot] = make_float4(f1, fx_row0(d0, beta), fx_ratio(d0, beta), __int_as_float(packed));
       sv[slot] = c;
     }
   };
@@ -592,55 +564,37 @@ __global__ __launch_bounds__(SEG_BLOCK) void k_spread2d_seg(const Rec<float>* __
 
       // one record's taps: lane i takes LDS column col0 + i, rows row0 .. row0
       // + 2W - 1 (clipped to the LDS tile when clip)
-      auto splat = [&](float2 f, int packed, float2 c, bool clip) {
+      auto splat = [&](float4 geo, float2 c, bool clip) {
+        const int packed = __float_as_int(geo.w);
         const int col = (packed >> 16) + i;
         if (col < 0 || col >= SEG_COLS) return;
         const int row0 = (int)(int16_t)(packed & 0xffff);
-        const float d1 = (float)(i - W + 1) - f.y;
-        int j0 = 0, j1 = L;
-        if (clip) {
-          j0 = max(0, -row0);
-          j1 = min(L, ROWS - row0);
-        }
-        const float d0 = (float)(1 - W + j0) - f.x;
-        const float w10 = __expf(-beta * (d1 * d1 + d0 * d0)) * scale;
-        float q = __expf(-beta * (2.f * d0 + 1.f));
-        float pr = c.x * w10, pi = c.y * w10;
-        unsigned long long* dst = acc + (row0 + j0) * TP + col;
+        const float w = fx_first((float)(i - W + 1) - geo.x, beta, geo.y, scale);
+        float pr = c.x * w, pi = c.y * w;
         if (!clip) {
-#pragma unroll
-          for (int j = 0; j < L; ++j) {
-            __hip_atomic_fetch_add(dst + j * TP, fx_pack(pr, pi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            pr *= q;
-            pi *= q;
-            q *= e2b;
-          }
+          fx_column<L>(acc + row0 * TP + col, TP, pr, pi, geo.z, e2b);
         } else {
-          for (int j = j0; j < j1; ++j) {
-            __hip_atomic_fetch_add(dst, fx_pack(pr, pi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            dst += TP;
+          const int j1 = min(row0 + L, ROWS);
+          float q = geo.z;
+          for (int j = max(row0, 0); j < j1; ++j) {
+            __hip_atomic_fetch_add(acc + j * TP + col, fx_pack(pr, pi), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
             pr *= q;
             pi *= q;
             q *= e2b;
           }
         }
       };
-      // taps of the staged records: home ones, then clipped ones; the RPW
-      // records of one pass are n / RPW apart (neighbouring samples of a pulse
-      // overlap and would meet on the same LDS banks)
+      // taps of the staged records: home ones, then clipped ones
       auto taps = [&]() {
         const int nh = ncount[0], ncl = ncount[1];
-        const int nph = (nh + RPW - 1) / RPW;
-        for (int pass = wave; pass < nph; pass += NWAVES) {
-          const int r = s * nph + pass;
-          if (s < RPW && r < nh) splat(sf[r], sc[r], sv[r], false);
-        }
+        fx_pass<RPW, NWAVES>(sgeo, sv, nh, wave, s, [&](float4 g, float2 v) { splat(g, v, false); });
         const int npc = (ncl + RPW - 1) / RPW;
         for (int pass = wave; pass < npc; pass += NWAVES) {
           const int r = s * npc + pass;
           if (s < RPW && r < ncl) {
             const int q = SEG_BLOCK - 1 - r;
-            splat(sf[q], sc[q], sv[q], true);
+            splat(sgeo[q], sv[q], true);
           }
         }
       };
