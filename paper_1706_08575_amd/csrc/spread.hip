@@ -17,10 +17,12 @@
 //     one 64-bit LDS integer add per complex tap (see the block comment of
 //     that kernel); on gfx950 the float32 LDS atomic add retires about 0.33
 //     lanes per clock per CU and the 64-bit integer one about 9.9 (measured);
-//   * float64 plans, and float32 plans that ask for it (k_spread2d,
-//     k_spread1d): float64 LDS words with ds_add_f64; with lds_copies > 1
-//     wave w accumulates into partial tile w % copies and the partial tiles
-//     are combined at the flush with compensated (TwoSum) addition.
+//   * float64 plans, and float32 plans that ask for it: matrix products in
+//     float64 (k_spread2d_mm, one partial tile of 32 or 64 cells), else
+//     float64 LDS words with ds_add_f64 (k_spread2d, k_spread1d); with
+//     lds_copies > 1 wave w accumulates into partial tile w % copies and the
+//     partial tiles are combined at the flush with compensated (TwoSum) addition.
+#include <cmath>
 #include <type_traits>
 
 #include "ftcg_internal.h"
@@ -59,6 +61,204 @@ __device__ inline real sum_copies(const real* base, int copy_stride, int copies)
     s = t;
   }
   return s + comp;
+}
+
+// ---------------------------------------------------------------------------
+// float64 tile accumulation as a matrix product (one partial tile)
+//
+// A record's taps are an outer product of its 2W row factors and its 2W column
+// factors times the value, so the tile is R C with R (rows x records) and C
+// (records x columns, complex). One wavefront owns 16 x 16 cells (or several
+// such blocks at tile 64) and runs v_mfma_f64_16x16x4 over the records whose
+// footprint meets its block, four at a time: lane l supplies the row factor
+// of cell row l % 16 and the column factor of cell column l % 16 of record
+// l / 16, 0 outside the footprint. The factors of a chunk of MM_CH records
+// are formed once, one record per lane and half an axis per wavefront (so a
+// recursion runs over at most W of them), and stored record-minor with an odd
+// pitch: conflict-free to write, and the 16 cells of a record read from 16
+// different banks. With ds_add_f64 instead (k_spread2d) the LDS atomics bound
+// the kernel, at about 10 cycles per 64 lanes of which 44 % were masked by the
+// tile's edges, 72 cycles a record and CU. 611 x 1237 samples on 1000^2, G =
+// 2048, W = 6, tile 32: 110 us against 185; 2^21 on 1024^2, spread and FFT: 329
+// against 507 (tile 64: 402 against 645). Now the matrix unit (a third of the
+// time), the factors' exponentials (as much) and the loads' latency share it.
+// With the accumulators in the accumulation registers (the compiler's choice
+// without the launch bound) 139 us.
+//
+// Non-finite values stay out of the products (0 times infinity would reach
+// the whole block) and are added cell by cell.
+// ---------------------------------------------------------------------------
+constexpr int MM_CH = 64;
+typedef double mm_acc __attribute__((ext_vector_type(4)));
+
+template <int T>
+struct MmTile {
+  static constexpr int NB = T / 16;            // blocks per axis
+  static constexpr int NW = 4;                 // wavefronts
+  static constexpr int BPW = NB * NB / NW;     // blocks per wavefront
+};
+
+template <class real, int W, int T, bool REAL>
+__global__ __launch_bounds__(64 * MmTile<T>::NW, T == 64 ? 3 : 6) void k_spread2d_mm(
+    const Rec<real>* __restrict__ recs, const real* __restrict__ alpha_s, const int32_t* __restrict__ tile_off,
+    const std::conditional_t<REAL, real, typename Cx<real>::t>* __restrict__ fhat,
+    std::conditional_t<REAL, real, typename Cx<real>::t>* __restrict__ grid, int64_t G, int nt, real beta, real e2b) {
+  using cx = std::conditional_t<REAL, real, typename Cx<real>::t>;
+  using fac = std::conditional_t<REAL, double, double2>;
+  constexpr int L = 2 * W;
+  constexpr int BPW = MmTile<T>::BPW, NB = MmTile<T>::NB;
+  constexpr int PITCH = MM_CH + 1;
+  constexpr int NC = REAL ? 1 : 2;
+  __shared__ double frow[L * PITCH];
+  __shared__ fac fcol[L * PITCH];
+  __shared__ int first[MM_CH];    // first row | first column << 16 (signed, tile cells)
+  __shared__ int finite[MM_CH];
+  const int tile = blockIdx.x;
+  const int t0 = tile / nt, t1 = tile - (tile / nt) * nt;
+  const int beg = tile_off[tile], end = tile_off[tile + 1];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int l16 = lane & 15, l4 = lane >> 4;
+  mm_acc acc[BPW][NC] = {};
+  Rec<real> next = {};   // read one chunk ahead
+  if (beg < end) next = recs[beg + min(lane, end - beg - 1)];
+  for (int cb = beg; cb < end; cb += MM_CH) {
+    const int cn = min(end - cb, MM_CH);
+    __syncthreads();   // every wavefront has left the previous chunk
+    {
+      const int r = cb + min(lane, cn - 1);
+      const Rec<real> rec = next;
+      next = recs[min(cb + MM_CH + lane, end - 1)];
+      {
+        const int part = wave;           // rows, columns: two halves each
+        const int j0 = (part & 1) * W;   // half of the axis: factors j0 .. j0 + W - 1
+        const real d = (real)(j0 + 1 - W) - (part < 2 ? rec.f0 : rec.f1);
+        real e = kexp(-beta * d * d), q = kexp(-beta * (2 * d + 1));
+        if (part < 2) {
+#pragma unroll
+          for (int j = 0; j < W; ++j) {
+            frow[(j0 + j) * PITCH + lane] = (double)e;
+            e *= q;
+            q *= e2b;
+          }
+          if (part == 0) {
+            const int c0 = (int)(int16_t)(rec.c01 & 0xffff) - W + 1, c1 = (rec.c01 >> 16) - W + 1;
+            first[lane] = (int)(((uint32_t)c0 & 0xffffu) | ((uint32_t)c1 << 16));
+          }
+        } else {
+          cx v = fhat[rec.src];
+          bool fin;
+          if constexpr (REAL) {
+            fin = isfinite(v);
+          } else {
+            const real a = alpha_s[r];
+            v.x *= a;
+            v.y *= a;
+            fin = isfinite(v.x) && isfinite(v.y);
+          }
+          if (part == 2) finite[lane] = fin ? 1 : 0;
+#pragma unroll
+          for (int j = 0; j < W; ++j) {
+            if constexpr (REAL)
+              fcol[(j0 + j) * PITCH + lane] = (double)e * (double)v;
+            else
+              fcol[(j0 + j) * PITCH + lane] = make_double2((double)e * (double)v.x, (double)e * (double)v.y);
+            e *= q;
+            q *= e2b;
+          }
+        }
+      }
+    }
+    __syncthreads();
+    const int own = first[lane];
+    const int own0 = (int)(int16_t)(own & 0xffff), own1 = own >> 16;
+    const bool ok = finite[lane] != 0;
+#pragma unroll
+    for (int b = 0; b < BPW; ++b) {
+      const int blk = wave * BPW + b;
+      const int row0 = (blk / NB) * 16, col0 = (blk % NB) * 16;
+      const bool meets = lane < cn && own0 < row0 + 16 && own0 + L > row0 && own1 < col0 + 16 && own1 + L > col0;
+      const unsigned long long take = __ballot(meets && ok);
+      unsigned long long odd = __ballot(meets && !ok);
+      // records to take, in lanes 0 .. n - 1 (the others behind them: a permutation)
+      const unsigned long long below = (1ull << lane) - 1ull;
+      const int n = __popcll(take);
+      const int to = (take >> lane) & 1 ? __popcll(take & below) : n + __popcll(~take & below);
+      const int list = __builtin_amdgcn_ds_permute(to * 4, lane | ((own0 + 64) << 8) | ((own1 + 64) << 16));
+      for (int g = 0; g < n; g += 4) {
+        const int e = __shfl(list, g + l4);
+        const bool live = g + l4 < n;
+        const int rec = e & 0xff;
+        const int j0 = row0 + l16 - (((e >> 8) & 0xff) - 64), j1 = col0 + l16 - ((e >> 16) - 64);
+        const double fr = frow[min(max(j0, 0), L - 1) * PITCH + rec];
+        const fac fc = fcol[min(max(j1, 0), L - 1) * PITCH + rec];
+        const bool in0 = live && (unsigned)j0 < (unsigned)L, in1 = live && (unsigned)j1 < (unsigned)L;
+        const double ra = in0 ? fr : 0.0;
+        if constexpr (REAL) {
+          acc[b][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ra, in1 ? fc : 0.0, acc[b][0], 0, 0, 0);
+        } else {
+          acc[b][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ra, in1 ? fc.x : 0.0, acc[b][0], 0, 0, 0);
+          acc[b][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ra, in1 ? fc.y : 0.0, acc[b][1], 0, 0, 0);
+        }
+      }
+      while (odd) {
+        const int rec = __ffsll(odd) - 1;
+        odd &= odd - 1;
+        const int o = first[rec];
+        const int j1 = col0 + l16 - (o >> 16);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int j0 = row0 + 4 * v + l4 - (int)(int16_t)(o & 0xffff);
+          if ((unsigned)j0 < (unsigned)L && (unsigned)j1 < (unsigned)L) {
+            const double fr = frow[j0 * PITCH + rec];
+            const fac fc = fcol[j1 * PITCH + rec];
+            if constexpr (REAL) {
+              acc[b][0][v] += fr * fc;
+            } else {
+              acc[b][0][v] += fr * fc.x;
+              acc[b][1][v] += fr * fc.y;
+            }
+          }
+        }
+      }
+    }
+  }
+  cx* out = grid + (int64_t)t0 * T * G + (int64_t)t1 * T;
+#pragma unroll
+  for (int b = 0; b < BPW; ++b) {
+    const int blk = wave * BPW + b;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = (blk / NB) * 16 + 4 * v + l4, col = (blk % NB) * 16 + l16;
+      cx o;
+      if constexpr (REAL) {
+        o = (real)acc[b][0][v];
+      } else {
+        o.x = (real)acc[b][0][v];
+        o.y = (real)acc[b][1][v];
+      }
+      out[(int64_t)row * G + col] = o;
+    }
+  }
+}
+
+// true when the kernel above took the launch: one partial tile of 32 or 64
+// cells. At 16 a block is the whole tile: one wavefront per workgroup and 19 KiB
+// of LDS leave too few of them, and the LDS-atomic kernel stays.
+template <class real, int W, bool REAL, class Val>
+static bool launch_mm(ftcg_plan p, const Val* val, Val* grid) {
+  if (p->lds_copies != 1) return false;
+  auto go = [&](auto kernel, int nw) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)p->ntiles), dim3(64 * nw), 0, p->stream, p->recs.as<Rec<real>>(),
+                       p->alpha_s.as<real>(), p->tile_off.as<int32_t>(), val, grid, p->G, (int)p->nt, (real)p->beta,
+                       (real)std::exp(-2 * p->beta));
+    FTCG_HIP(hipGetLastError());
+    return true;
+  };
+  switch (p->tile) {
+    case 32: return go(k_spread2d_mm<real, W, 32, REAL>, MmTile<32>::NW);
+    case 64: return go(k_spread2d_mm<real, W, 64, REAL>, MmTile<64>::NW);
+    default: return false;
+  }
 }
 
 // REAL: weight 1, real values and a real grid (the density iterations): one
@@ -788,6 +988,7 @@ static void launch_spread_w(ftcg_plan p, const void* fhat, void* grid) {
   const real beta = (real)p->beta;
   const int copies = p->lds_copies;
   if (p->dim == 2) {
+    if (launch_mm<real, W, false>(p, static_cast<const cx*>(fhat), static_cast<cx*>(grid))) return;
     const size_t lds = (size_t)copies * 2 * T * (T + 1) * sizeof(double);
     static bool attr_done = false;
     if (!attr_done) {
@@ -831,6 +1032,7 @@ static void launch_spread_real(ftcg_plan p, const void* val, void* grid) {
       return;
     }
   }
+  if (launch_mm<real, W, true>(p, static_cast<const real*>(val), static_cast<real*>(grid))) return;
   const int copies = p->lds_copies;
   const size_t lds = (size_t)copies * T * (T + 1) * sizeof(double);
   FTCG_HIP(hipFuncSetAttribute((const void*)k_spread2d<real, W, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
