@@ -123,6 +123,7 @@ void set_points_begin(ftcg_plan p, int64_t m, const double* k_dev) {
   p->have_weights = false;
   p->finish_recs = false;
   p->weights_deferred = false;
+  p->deferred_spreads = 0;
   p->m = m;
   // 1) input check: finiteness, bounding box and the neighbour-bin
   //    geometry, reduced on the device; the check also zeroes the tile and

@@ -371,11 +371,13 @@ struct ftcg_plan_s {
   // set by the fused binning: the finish of the symmetric weight sum also
   // writes the record-order weights (through ws_inv) and then clears it
   bool finish_recs = false;
-  // the symmetric sum's finish is pending (fused-binning grids): the
-  // fixed-point spread forms each record's weight from ws_sum itself, and
-  // finish_deferred_weights writes alpha and the records' weights when
-  // anything else needs them
+  // the symmetric sum's finish is pending (fused-binning grids): the 2D
+  // spread of one partial tile forms each record's weight from ws_sum itself,
+  // and finish_deferred_weights writes alpha and the records' weights when
+  // anything else needs them, or when the points have served as many spreads
+  // as settle_weights allows
   bool weights_deferred = false;
+  int deferred_spreads = 0;   // spreads that formed the weights so far
   ftcg::WBinGeom wgeom{};
   bool have_wbins = false;
   bool weights_only = false;  // internal plans that only compute weights (no tile binning)

@@ -63,6 +63,14 @@ __device__ inline real sum_copies(const real* base, int copy_stride, int copies)
   return s + comp;
 }
 
+// Where the 2D kernels take values and weights from: FX_RECS, record r has weight
+// alpha_s[r]; FX_SUMS, the records carry no weights yet, and record r of sample
+// j takes alpha_j = pi^2 pi^2 / wsum[inv[j]] (bin-order sums of the symmetric
+// weight kernel, the same float64 division its finish does, rounded to the
+// records' type); FX_REAL, weight 1, real values and a real grid (the density
+// iterations).
+enum FxSrc { FX_RECS = 0, FX_SUMS = 1, FX_REAL = 2 };
+
 // ---------------------------------------------------------------------------
 // float64 tile accumulation as a matrix product (one partial tile)
 //
@@ -98,11 +106,15 @@ struct MmTile {
   static constexpr int BPW = NB * NB / NW;     // blocks per wavefront
 };
 
-template <class real, int W, int T, bool REAL>
+template <class real, int SRC>
+using MmValue = std::conditional_t<SRC == FX_REAL, real, typename Cx<real>::t>;
+
+template <class real, int W, int T, int SRC>
 __global__ __launch_bounds__(64 * MmTile<T>::NW, T == 64 ? 3 : 6) void k_spread2d_mm(
-    const Rec<real>* __restrict__ recs, const real* __restrict__ alpha_s, const int32_t* __restrict__ tile_off,
-    const std::conditional_t<REAL, real, typename Cx<real>::t>* __restrict__ fhat,
-    std::conditional_t<REAL, real, typename Cx<real>::t>* __restrict__ grid, int64_t G, int nt, real beta, real e2b) {
+    const Rec<real>* __restrict__ recs, const real* __restrict__ alpha_s, const double* __restrict__ wsum,
+    const int32_t* __restrict__ inv, const int32_t* __restrict__ tile_off, const MmValue<real, SRC>* __restrict__ fhat,
+    MmValue<real, SRC>* __restrict__ grid, int64_t G, int nt, real beta, real e2b) {
+  constexpr bool REAL = SRC == FX_REAL;
   using cx = std::conditional_t<REAL, real, typename Cx<real>::t>;
   using fac = std::conditional_t<REAL, double, double2>;
   constexpr int L = 2 * W;
@@ -150,7 +162,11 @@ __global__ __launch_bounds__(64 * MmTile<T>::NW, T == 64 ? 3 : 6) void k_spread2
           if constexpr (REAL) {
             fin = isfinite(v);
           } else {
-            const real a = alpha_s[r];
+            real a;
+            if constexpr (SRC == FX_SUMS)
+              a = (real)(wscale<2>() / wsum[inv[rec.src]]);
+            else
+              a = alpha_s[r];
             v.x *= a;
             v.y *= a;
             fin = isfinite(v.x) && isfinite(v.y);
@@ -244,19 +260,20 @@ __global__ __launch_bounds__(64 * MmTile<T>::NW, T == 64 ? 3 : 6) void k_spread2
 // true when the kernel above took the launch: one partial tile of 32 or 64
 // cells. At 16 a block is the whole tile: one wavefront per workgroup and 19 KiB
 // of LDS leave too few of them, and the LDS-atomic kernel stays.
-template <class real, int W, bool REAL, class Val>
+template <class real, int W, int SRC, class Val>
 static bool launch_mm(ftcg_plan p, const Val* val, Val* grid) {
   if (p->lds_copies != 1) return false;
   auto go = [&](auto kernel, int nw) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)p->ntiles), dim3(64 * nw), 0, p->stream, p->recs.as<Rec<real>>(),
-                       p->alpha_s.as<real>(), p->tile_off.as<int32_t>(), val, grid, p->G, (int)p->nt, (real)p->beta,
+                       p->alpha_s.as<real>(), p->ws_sum.as<double>(), p->ws_inv.as<int32_t>(),
+                       p->tile_off.as<int32_t>(), val, grid, p->G, (int)p->nt, (real)p->beta,
                        (real)std::exp(-2 * p->beta));
     FTCG_HIP(hipGetLastError());
     return true;
   };
   switch (p->tile) {
-    case 32: return go(k_spread2d_mm<real, W, 32, REAL>, MmTile<32>::NW);
-    case 64: return go(k_spread2d_mm<real, W, 64, REAL>, MmTile<64>::NW);
+    case 32: return go(k_spread2d_mm<real, W, 32, SRC>, MmTile<32>::NW);
+    case 64: return go(k_spread2d_mm<real, W, 64, SRC>, MmTile<64>::NW);
     default: return false;
   }
 }
@@ -369,15 +386,10 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d(const Rec<real>* __re
 // flush); columns outside the tile are skipped per lane.
 // ---------------------------------------------------------------------------
 
-// SRC: FX_RECS, record r has weight alpha_s[r]; FX_SUMS, the records carry no
-// weights yet, and record r of sample j takes alpha_j = pi^2 pi^2 / wsum[inv[j]]
-// (bin-order sums of the symmetric weight kernel, the same float64 division
-// its finish does), rounded to float32; FX_REAL, weight 1, real values and
-// a real grid (the density iterations): the cells are the low words of the
+// FX_REAL: the cells are the low words of the
 // packed ones, added with 32-bit LDS atomics (14.5 instead of 9.9 lanes per
 // clock, and no packing), the sums bit for bit the real parts of the complex form.
 // 512^2 raster, 2^17 samples: 15.2 against 20.9 us.
-enum FxSrc { FX_RECS = 0, FX_SUMS = 1, FX_REAL = 2 };
 template <int SRC>
 struct FxTypes {
   using val = float2;
@@ -976,19 +988,46 @@ static void launch_fx_t(ftcg_plan p, const void* fhat, void* grid) {
   FTCG_HIP(hipGetLastError());
 }
 
+// Spreads that form the weights themselves (about 8 % of a call: two gathers
+// and a division a record) before the finish is worth its launch: points that
+// serve one spread never need it, points that serve many spread from the
+// records' weights. The finish costs about two such spreads' extra (1M samples
+// on 1024^2: 18 us against 8 a spread, 128 and 120 us a call; 756k in float64
+// 18 against 10, 160 and 150), so the third takes it. A call being captured
+// leaves the plan as it is, because what it records has not run when the next
+// call reads the weights.
+constexpr int DEFERRED_SPREADS = 2;
+static void settle_weights(ftcg_plan p) {
+  if (!p->weights_deferred) return;
+  if (p->deferred_spreads < DEFERRED_SPREADS) {
+    ++p->deferred_spreads;
+    return;
+  }
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(p->stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  if (st == hipStreamCaptureStatusNone) finish_deferred_weights(p);
+}
+
 template <class real, int W>
 static void launch_spread_w(ftcg_plan p, const void* fhat, void* grid) {
   using cx = typename Cx<real>::t;
   const int T = p->tile;
+  settle_weights(p);
   if (std::is_same<real, float>::value && p->dim == 2 && p->accum == ACCUM_FIXED) {
     launch_fx_t<W>(p, fhat, grid);   // forms deferred weights itself
     return;
   }
+  if (p->dim == 2 && p->weights_deferred &&
+      launch_mm<real, W, FX_SUMS>(p, static_cast<const cx*>(fhat), static_cast<cx*>(grid)))
+    return;
   finish_deferred_weights(p);          // the other kernels read the records' weights
   const real beta = (real)p->beta;
   const int copies = p->lds_copies;
   if (p->dim == 2) {
-    if (launch_mm<real, W, false>(p, static_cast<const cx*>(fhat), static_cast<cx*>(grid))) return;
+    if (launch_mm<real, W, FX_RECS>(p, static_cast<const cx*>(fhat), static_cast<cx*>(grid))) return;
     const size_t lds = (size_t)copies * 2 * T * (T + 1) * sizeof(double);
     static bool attr_done = false;
     if (!attr_done) {
@@ -1032,7 +1071,7 @@ static void launch_spread_real(ftcg_plan p, const void* val, void* grid) {
       return;
     }
   }
-  if (launch_mm<real, W, true>(p, static_cast<const real*>(val), static_cast<real*>(grid))) return;
+  if (launch_mm<real, W, FX_REAL>(p, static_cast<const real*>(val), static_cast<real*>(grid))) return;
   const int copies = p->lds_copies;
   const size_t lds = (size_t)copies * T * (T + 1) * sizeof(double);
   FTCG_HIP(hipFuncSetAttribute((const void*)k_spread2d<real, W, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
