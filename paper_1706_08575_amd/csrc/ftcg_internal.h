@@ -377,6 +377,7 @@ struct ftcg_plan_s {
   // anything else needs them, or when the points have served as many spreads
   // as settle_weights allows
   bool weights_deferred = false;
+  bool alpha_by_src = false;  // the records carry no weights: the 1D spread reads alpha[src]
   int deferred_spreads = 0;   // spreads that formed the weights so far
   ftcg::WBinGeom wgeom{};
   bool have_wbins = false;
@@ -428,6 +429,7 @@ struct ftcg_plan_s {
   struct PendingPoints {
     int seq = 0;
     bool tiles = false, early_scatter = false, fused = false, band = false;
+    bool small = false;   // small_1d_points did all of it
   } pending;
 };
 
@@ -457,6 +459,8 @@ void setup_weight_bins(ftcg_plan p);                 // buffers for the geometry
 void sort_weight_rows(ftcg_plan p);                  // 2D bins from the rows (+ sin/cos)
 void build_weight_bins_1d(ftcg_plan p, const double* k);   // 1D sorted neighbour bins
 void run_plain_weights(ftcg_plan p);                // alpha (caller order) from the bins
+bool small_1d(const ftcg_plan_s* p);                // 1D plain weights and binning in one launch
+void small_1d_points(ftcg_plan p, const double* k, int seq);
 void finish_deferred_weights(ftcg_plan p);          // no-op unless p->weights_deferred
 // ftcg_set_points in two parts (a batch enqueues every item's first part
 // before the host waits for the first input check); throw on errors

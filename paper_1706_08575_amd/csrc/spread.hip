@@ -877,10 +877,12 @@ __global__ __launch_bounds__(SEG_BLOCK) void k_spread2d_seg(const Rec<float>* __
   }
 }
 
-// 1D: one thread per record walks its 2W taps
+// 1D: one thread per record walks its 2W taps; weights in record order, or
+// (alpha given) in caller order
 template <class real, int W>
 __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread1d(const Rec<real>* __restrict__ recs,
                                                            const real* __restrict__ alpha_s,
+                                                           const double* __restrict__ alpha,
                                                            const int32_t* __restrict__ tile_off,
                                                            const typename Cx<real>::t* __restrict__ fhat,
                                                            typename Cx<real>::t* __restrict__ grid, int T, int copies,
@@ -899,7 +901,7 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread1d(const Rec<real>* __re
   const real e2b = kexp(-2 * beta);
   for (int r = beg + tid; r < end; r += SPREAD_BLOCK) {
     const Rec<real> rec = recs[r];
-    const real a = alpha_s[r];
+    const real a = alpha ? (real)alpha[rec.src] : alpha_s[r];
     const cx v = fhat[rec.src];
     const int c0 = (int)(int16_t)(rec.c01 & 0xffff);
     const real d0 = (real)(1 - W) - rec.f0;
@@ -1041,7 +1043,8 @@ static void launch_spread_w(ftcg_plan p, const void* fhat, void* grid) {
   } else {
     const size_t lds = (size_t)copies * 2 * T * sizeof(double);
     hipLaunchKernelGGL((k_spread1d<real, W>), dim3((unsigned)p->ntiles), dim3(SPREAD_BLOCK), lds, p->stream,
-                       p->recs.as<Rec<real>>(), p->alpha_s.as<real>(), p->tile_off.as<int32_t>(),
+                       p->recs.as<Rec<real>>(), p->alpha_s.as<real>(),
+                       p->alpha_by_src ? p->alpha.as<double>() : nullptr, p->tile_off.as<int32_t>(),
                        static_cast<const cx*>(fhat), static_cast<cx*>(grid), T, copies, beta);
   }
   FTCG_HIP(hipGetLastError());
