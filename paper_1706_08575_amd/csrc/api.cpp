@@ -160,11 +160,8 @@ void set_points_begin(ftcg_plan p, int64_t m, const double* k_dev) {
     zero_b = p->wb_cnt.as<int32_t>();
     zero_nb = WROW_CNT_ZERO;
   }
-  auto* part = p->check_part.as<unsigned long long>();
-  const int nparts = launch_check_points(p, k_dev, m, part, zero_ptr, zero_n, zero_b, zero_nb);
-  const int seq = ++p->check_seq;
-  p->pending.seq = seq;
-  launch_check_reduce(p, part, nparts, seq);
+  p->pending.seq = ++p->check_seq;
+  launch_check_points(p, k_dev, m, p->pending.seq, zero_ptr, zero_n, zero_b, zero_nb);
   timing_end(p, STEP_BIN);
   FTCG_HIP(hipEventRecord(p->ev_check, p->stream));
   // 2) binning passes that need no host decision are enqueued before the
@@ -380,6 +377,8 @@ ftcg_status ftcg_plan_create(ftcg_plan* out, int dim, const int64_t* n, int half
       throw StatusError{FTCG_ENOMEM};
     }
     p->check_part.ensure(sizeof(unsigned long long) * 5 * CHECK_PARTS);
+    p->tickets.ensure(sizeof(int32_t));
+    FTCG_HIP(hipMemsetAsync(p->tickets.p, 0, sizeof(int32_t), p->stream));
     p->geo.ensure(sizeof(CheckOut));
     if (hipHostMalloc((void**)&p->host_geo, sizeof(CheckOut), hipHostMallocCoherent) != hipSuccess) {
       p->host_geo = nullptr;
@@ -398,7 +397,7 @@ ftcg_status ftcg_plan_create(ftcg_plan* out, int dim, const int64_t* n, int half
 ftcg_status ftcg_plan_destroy(ftcg_plan p) {
   if (!p) return FTCG_EINVAL;
   (void)hipStreamSynchronize(p->stream);
-  DevBuf* bufs[] = {&p->fa_gl, &p->fa_G, &p->fa_A, &p->fa_diag, &p->fa_beta, &p->fa_tw, &p->fa_tmp, &p->fa_T, &p->den_val, &p->den_d, &p->band_P, &p->band_col, &p->band_far, &p->band_c, &p->alpha,  &p->recs,  &p->alpha_s, &p->tile_cnt, &p->tile_off, &p->scan_tmp, &p->tile_scan_tmp, &p->check_part, &p->geo,
+  DevBuf* bufs[] = {&p->fa_gl, &p->fa_G, &p->fa_A, &p->fa_diag, &p->fa_beta, &p->fa_tw, &p->fa_tmp, &p->fa_T, &p->den_val, &p->den_d, &p->band_P, &p->band_col, &p->band_far, &p->band_c, &p->alpha,  &p->recs,  &p->alpha_s, &p->tile_cnt, &p->tile_off, &p->scan_tmp, &p->tile_scan_tmp, &p->check_part, &p->tickets, &p->geo,
                     &p->flags,  &p->wb_cnt, &p->wb_off, &p->wb_rowoff, &p->wb_rowbuf, &p->ws_k,   &p->ws_idx,   &p->wb_of, &p->ws_inv, &p->ws_sum, &p->audit_buf,
                     &p->grid,   &p->fft_tmp, &p->deapod, &p->twiddle, &p->tile_order};
   for (DevBuf* b : bufs) b->release();

@@ -420,6 +420,7 @@ struct ftcg_plan_s {
   // device, its pinned coherent host copy (written by the same kernel), and
   // the event after it, which is all the host waits for
   ftcg::DevBuf check_part;
+  ftcg::DevBuf tickets;      // arrival counter of the launches whose last workgroup goes on; 0 between them
   ftcg::DevBuf geo;
   ftcg::CheckOut* host_geo = nullptr;
   hipEvent_t ev_check = nullptr;
@@ -440,10 +441,8 @@ constexpr size_t FLAGS_BYTES = 128;       // device flags / pinned host mirror
 constexpr int64_t WROW_CNT_ZERO = 4100;   // bin-row counters cleared by the input check (>= WROW_MAX + 1)
 constexpr int CHECK_PARTS = 1024;         // input-check workgroups at most
 // returns the number of partial records (5 words each) written to part
-int launch_check_points(ftcg_plan p, const double* k, int64_t m, unsigned long long* part, int32_t* zero_a,
-                        int64_t zero_na, int32_t* zero_b, int64_t zero_nb);
-// reduces the partials into p->geo and p->host_geo (one workgroup)
-void launch_check_reduce(ftcg_plan p, const unsigned long long* part, int nparts, int seq);
+void launch_check_points(ftcg_plan p, const double* k, int64_t m, int seq, int32_t* zero_a, int64_t zero_na,
+                         int32_t* zero_b, int64_t zero_nb);
 void bin_points_k(ftcg_plan p, const double* k);   // fills recs, alpha_s, tile_off
 void bin_count_k(ftcg_plan p, const double* k);    // its counting + scan (tile_off, cursors)
 void bin_scatter_k(ftcg_plan p, const double* k);  // its scatter (recs, alpha_s)

@@ -131,15 +131,16 @@ __device__ inline CheckOut check_finish(const unsigned long long (&v)[5], int di
     // h = R / span exactly, so the 2 span + 1 bins of a row range end on the
     // box of radius R; at most max_bins bins per axis
     double vol = 1.0;
-    for (int a = 0; a < dim; ++a) vol *= fmax(o.kmax[a] - o.kmin[a], 1e-9);
+    for (int a = 0; a < 2; ++a)
+      if (a < dim) vol *= fmax(o.kmax[a] - o.kmin[a], 1e-9);
     const double rho = (double)m / vol;
     const double h_target = dim == 2 ? sqrt(BIN_TARGET / rho) : BIN_TARGET / rho;
     const double sp = fmin(fmax(floor(R / h_target + 0.5), 2.0), 16.0);
     double h = R / sp;
     const double max_bins = dim == 1 ? (double)(1 << 22) : (double)WROW_MAX;
-    for (int a = 0; a < dim; ++a) {
+    for (int a = 0; a < 2; ++a) {
       const double ext = o.kmax[a] - o.kmin[a];
-      if (ext / h + 1.0 > max_bins) h = ext / (max_bins - 1.0);
+      if (a < dim && ext / h + 1.0 > max_bins) h = ext / (max_bins - 1.0);
     }
     g.h = h;
     g.span = (int)ceil(R / h);

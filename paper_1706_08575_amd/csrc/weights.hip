@@ -655,64 +655,6 @@ __global__ __launch_bounds__(WB_BLOCK) void k_frame_weights_at(const int32_t* __
   if (lane == 0) out[w] = wscale<DIM>() / acc;
 }
 
-// Second step of the input check: one workgroup reduces the partials of
-// k_check_points, rejects the points when one is non-finite or farther than
-// 2^40 from the origin on an axis, and derives the neighbour-bin geometry
-// from the bounding box. The result goes to device memory, for the binning
-// passes enqueued before the host has looked at it, and to pinned host
-// memory, from which the host launches the rest with the same values. A
-// rejected set still gets a valid one-bin geometry, so those passes stay in
-// bounds.
-constexpr int CR_BLOCK = 256;
-__global__ __launch_bounds__(CR_BLOCK) void k_check_reduce(const unsigned long long* __restrict__ part, int nparts,
-                                                           int dim, int64_t m, double R, int seq,
-                                                           CheckOut* __restrict__ out_dev,
-                                                           CheckOut* __restrict__ out_host) {
-  __shared__ unsigned long long sred[5][CR_BLOCK / 64];
-  unsigned long long v[5] = {0ull, ~0ull, ~0ull, 0ull, 0ull};   // flag, lo0, lo1, hi0, hi1
-  for (int b = threadIdx.x; b < nparts; b += CR_BLOCK) {
-    const unsigned long long* q = part + 5 * b;
-    v[0] |= q[0];
-    v[1] = q[1] < v[1] ? q[1] : v[1];
-    v[2] = q[2] < v[2] ? q[2] : v[2];
-    v[3] = q[3] > v[3] ? q[3] : v[3];
-    v[4] = q[4] > v[4] ? q[4] : v[4];
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    unsigned long long y[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) y[i] = __shfl_xor(v[i], off, 64);
-    v[0] |= y[0];
-    v[1] = y[1] < v[1] ? y[1] : v[1];
-    v[2] = y[2] < v[2] ? y[2] : v[2];
-    v[3] = y[3] > v[3] ? y[3] : v[3];
-    v[4] = y[4] > v[4] ? y[4] : v[4];
-  }
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-    for (int i = 0; i < 5; ++i) sred[i][w] = v[i];
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  for (int q = 1; q < CR_BLOCK / 64; ++q) {
-    v[0] |= sred[0][q];
-    v[1] = sred[1][q] < v[1] ? sred[1][q] : v[1];
-    v[2] = sred[2][q] < v[2] ? sred[2][q] : v[2];
-    v[3] = sred[3][q] > v[3] ? sred[3][q] : v[3];
-    v[4] = sred[4][q] > v[4] ? sred[4][q] : v[4];
-  }
-  CheckOut o = check_finish(v, dim, m, R);
-  o.seq = seq;
-  *out_dev = o;
-  *out_host = o;
-}
-
-void launch_check_reduce(ftcg_plan p, const unsigned long long* part, int nparts, int seq) {
-  hipLaunchKernelGGL(k_check_reduce, dim3(1), dim3(CR_BLOCK), 0, p->stream, part, nparts, p->dim, p->m, p->R, seq,
-                     p->geo.as<CheckOut>(), p->host_geo);
-  FTCG_HIP(hipGetLastError());
-}
-
 // 2D neighbour binning in two levels, so no pass spreads atomics over all
 // nb0 x nb1 bins (they outgrow the L2 on large rasters) and no pass gathers
 // at random:
