@@ -108,6 +108,7 @@ __global__ __launch_bounds__(BATCH_BLOCK) void k_spread_persistent(const BatchTa
   __shared__ unsigned long long acc[ROWS * TP];
   __shared__ float4 sgeo[STG];   // f1, first row's kernel value, ratio of the rows, c01 (bits)
   __shared__ float2 sval[STG];   // alpha * fhat
+  __shared__ int ncount[2];
   __shared__ int task_sh;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int s = lane / L, i = lane - (lane / L) * L;
@@ -140,45 +141,45 @@ __global__ __launch_bounds__(BATCH_BLOCK) void k_spread_persistent(const BatchTa
     const float2* fhat = args->fhat + it.fhat_off;
     for (int idx = tid; idx < ROWS * TP; idx += BATCH_BLOCK) acc[idx] = 0ull;
     __syncthreads();
-    // one record's 2W x 2W taps: lane i takes footprint column i
-    auto splat = [&](float4 geo, float2 v) {
+    // one record's 2W (or, half, W) rows of 2W taps: lane i takes footprint column i
+    auto splat = [&](float4 geo, float2 v, auto half) {
+      constexpr int N = decltype(half)::value ? W : L;
       const int c01 = __float_as_int(geo.w);
       const int col = (c01 >> 16) - W + 1 + i;
       if (col < 0 || col >= T) return;
       const int c0 = (int)(int16_t)(c01 & 0xffff);
       const float w = fx_first((float)(i - W + 1) - geo.x, beta, geo.y, scale);
-      fx_column<L>(acc + (c0 - W + 1 + PAD) * TP + col, TP, v.x * w, v.y * w, geo.z, e2b);
+      fx_column<N>(acc + (c0 - W + 1 + PAD) * TP + col, TP, v.x * w, v.y * w, geo.z, e2b);
     };
-    auto record = [&](int r, float4& geo, float2& v) {
-      const Rec<float> rec = it.recs[r];
+    auto value = [&](int r, int src) {
       const float a = it.alpha_s[r];
-      const float2 f = fhat[rec.src];
-      const float d0 = (float)(1 - W) - rec.f0;
-      geo = make_float4(rec.f1, fx_row0(d0, beta), fx_ratio(d0, beta), __int_as_float(rec.c01));
-      v = make_float2(f.x * a, f.y * a);
+      const float2 f = fhat[src];
+      return make_float2(f.x * a, f.y * a);
     };
     if constexpr (STAGED) {
+      static_assert(FX_STAGE == BATCH_BLOCK, "one staged record per thread");
       for (int cb = tk.beg; cb < tk.end; cb += FX_STAGE) {
-        const int cn = min(tk.end - cb, FX_STAGE);
         if (cb != tk.beg) __syncthreads();   // every wavefront has left the previous chunk
-        for (int r = tid; r < cn; r += BATCH_BLOCK) {
-          float4 geo;
-          float2 v;
-          record(cb + r, geo, v);
-          sgeo[r] = geo;
-          sval[r] = v;
-        }
+        if (tid < 2) ncount[tid] = 0;
         __syncthreads();
-        fx_pass<RPW, NWAVES>(sgeo, sval, cn, wave, s, splat);
+        const bool live = cb + tid < tk.end;
+        const int r = live ? cb + tid : cb;
+        const Rec<float> rec = it.recs[r];
+        fx_put<W>(sgeo, sval, ncount, live, rec, value(r, rec.src), T, beta);
+        __syncthreads();
+        const int nw = ncount[0], nh = ncount[1];
+        fx_pass<RPW, NWAVES>(sgeo, sval, nw, wave, s, [&](float4 g, float2 v) { splat(g, v, std::false_type{}); });
+        fx_pass<RPW, NWAVES>(sgeo + (FX_STAGE - nh), sval + (FX_STAGE - nh), nh, wave, s,
+                             [&](float4 g, float2 v) { splat(g, v, std::true_type{}); });
       }
     } else {
       for (int base = tk.beg + wave * RPW; base < tk.end; base += NWAVES * RPW) {
         const int r = base + s;
         if (s < RPW && r < tk.end) {
-          float4 geo;
-          float2 v;
-          record(r, geo, v);
-          splat(geo, v);
+          const Rec<float> rec = it.recs[r];
+          const float d0 = (float)(1 - W) - rec.f0;
+          splat(make_float4(rec.f1, fx_row0(d0, beta), fx_ratio(d0, beta), __int_as_float(rec.c01)),
+                value(r, rec.src), std::false_type{});
         }
       }
     }

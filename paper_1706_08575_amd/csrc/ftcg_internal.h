@@ -187,6 +187,40 @@ __device__ inline void fx_column(unsigned* dst, int pitch, float p, float q, flo
 // samples: 0.73 -> 0.59 ms; on small grids the LDS atomics bound the loop).
 constexpr int FX_STAGE = 256;   // 6 KiB: keeps 7 workgroups of tile 32, W = 6 per CU
 
+// Puts a workgroup's records into the stage, one per thread (live: the thread has
+// one; every thread of a wavefront calls). A record with more than W of its 2W
+// rows inside the tile (0 .. T) goes to the front, with all its rows; one with W
+// or fewer (a quarter of them at tile 32, W = 6) to the back, with the W rows that
+// cover those, its factors and row shifted to the first of them. ncount: staged
+// so far at either end, 0 before. The geometry: f1, first row's kernel value,
+// ratio of the rows, and (bits) the local cell, the row of a back one shifted.
+// Without the lists every record walks 2W rows, those outside into halo rows that
+// are dropped: 1M samples on 1024^2 104 -> 96 us (records' weights), 2^17 on 512^2
+// 20.9 -> 20.4.
+template <int W, class Val>
+__device__ inline void fx_put(float4* sgeo, Val* sval, int* ncount, bool live, const Rec<float>& rec, Val v, int T,
+                              float beta) {
+  const int lane = threadIdx.x & 63;
+  const int c0 = (int)(int16_t)(rec.c01 & 0xffff), r0 = c0 - W + 1;
+  const bool top = r0 + W <= 0, half = top || T - r0 <= W;
+  const unsigned long long bw = __ballot(live && !half), bh = __ballot(live && half);
+  int basew = 0, baseh = 0;
+  if (lane == 0) {
+    if (bw) basew = atomicAdd(&ncount[0], __popcll(bw));
+    if (bh) baseh = atomicAdd(&ncount[1], __popcll(bh));
+  }
+  basew = __shfl(basew, 0);
+  baseh = __shfl(baseh, 0);
+  if (!live) return;
+  const int rank = __popcll((half ? bh : bw) & ((1ull << lane) - 1ull));
+  const int slot = half ? FX_STAGE - 1 - (baseh + rank) : basew + rank;
+  const int shift = top ? W : 0;
+  const float d0 = (float)(1 - W + shift) - rec.f0;
+  sgeo[slot] = make_float4(rec.f1, fx_row0(d0, beta), fx_ratio(d0, beta),
+                           __int_as_float((int)(((uint32_t)rec.c01 & 0xffff0000u) | ((uint32_t)(c0 + shift) & 0xffffu))));
+  sval[slot] = v;
+}
+
 // Taps of n staged records (n >= 0): NWAVES wavefronts take RPW records a pass,
 // n / RPW apart, since records next to each other come from neighbouring samples
 // of one pulse, whose footprints overlap, and in one pass they would meet on the

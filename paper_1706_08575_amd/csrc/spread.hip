@@ -454,6 +454,7 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
   __shared__ cell_t acc[ROWS * TP];
   __shared__ float4 sgeo[STG];          // f1, first row's kernel value, ratio of the rows, c01 (bits)
   __shared__ val_t sval[STG];           // alpha * fhat[src]
+  __shared__ int ncount[2];             // staged records: whole ones (from the front), halves (from the back)
   __shared__ float red[SPREAD_BLOCK / 64];
   __shared__ long long red2[SPREAD_BLOCK / 64];
 
@@ -474,15 +475,19 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
   // units of 2^-20 of that maximum. The first pass stages the first chunk.
   const int first = STAGED ? min(end - beg, STG) : 0;
   float mx = 0.f;
-  for (int r = beg + tid; r < end; r += SPREAD_BLOCK) {
+  val_t mine = {};   // of the staged record of this thread
+  if constexpr (STAGED) {
+    static_assert(FX_STAGE == SPREAD_BLOCK, "one staged record per thread");
+    if (tid < 2) ncount[tid] = 0;
+    __syncthreads();
+    const bool live = tid < first;
+    const int r = beg + (live ? tid : 0);
     const Rec<float> rec = recs[r];
-    const val_t v = value(r, rec.src);
-    if (r - beg < first) {
-      sgeo[r - beg] = geometry(rec);
-      sval[r - beg] = v;
-    }
-    mx = fmaxf(mx, size_of(v));
+    mine = value(r, rec.src);
+    fx_put<W>(sgeo, sval, ncount, live, rec, mine, T, beta);
+    if (live) mx = size_of(mine);
   }
+  for (int r = beg + first + tid; r < end; r += SPREAD_BLOCK) mx = fmaxf(mx, size_of(value(r, recs[r].src)));
   for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
   if (lane == 0) red[wave] = mx;
   for (int idx = tid; idx < ROWS * TP; idx += SPREAD_BLOCK) acc[idx] = 0;
@@ -503,14 +508,9 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
   }
   const float qs = 1048576.f / mx;
   long long qsum = 0;
-  for (int r = beg + tid; r < end; r += SPREAD_BLOCK) {
-    val_t v;
-    if (r - beg < first)   // staged by this thread in the first pass
-      v = sval[r - beg];
-    else
-      v = value(r, recs[r].src);
-    qsum += (long long)ceilf(size_of(v) * qs) + 1;
-  }
+  if (tid < first) qsum += (long long)ceilf(size_of(mine) * qs) + 1;
+  for (int r = beg + first + tid; r < end; r += SPREAD_BLOCK)
+    qsum += (long long)ceilf(size_of(value(r, recs[r].src)) * qs) + 1;
   for (int off = 32; off > 0; off >>= 1) qsum += __shfl_xor(qsum, off);
   __syncthreads();
   if (lane == 0) reinterpret_cast<long long*>(red2)[wave] = qsum;
@@ -525,8 +525,9 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
   const int s = lane / L, i = lane - (lane / L) * L;
   const float e2b = __expf(-2.f * beta);
   constexpr int NWAVES = SPREAD_BLOCK / 64;
-  // one record's 2W x 2W taps: lane i takes footprint column i
-  auto splat = [&](float4 geo, val_t v) {
+  // one record's 2W (or, half, W) rows of 2W taps: lane i takes footprint column i
+  auto splat = [&](float4 geo, val_t v, auto half) {
+    constexpr int N = decltype(half)::value ? W : L;
     const int c01 = __float_as_int(geo.w);
     const int col = (c01 >> 16) - W + 1 + i;
     if (col < 0 || col >= T) return;
@@ -534,30 +535,33 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
     const float w = fx_first((float)(i - W + 1) - geo.x, beta, geo.y, scale);
     cell_t* dst = acc + (c0 - W + 1 + PAD) * TP + col;
     if constexpr (REAL)
-      fx_column<L>(dst, TP, v * w, geo.z, e2b);
+      fx_column<N>(dst, TP, v * w, geo.z, e2b);
     else
-      fx_column<L>(dst, TP, v.x * w, v.y * w, geo.z, e2b);
+      fx_column<N>(dst, TP, v.x * w, v.y * w, geo.z, e2b);
   };
   if constexpr (STAGED) {
     for (int cb = beg; cb < end; cb += FX_STAGE) {
-      const int cn = min(end - cb, FX_STAGE);
       if (cb != beg) {   // later chunks: restage once every wavefront has left the previous one
         __syncthreads();
-        for (int r = tid; r < cn; r += SPREAD_BLOCK) {
-          const Rec<float> rec = recs[cb + r];
-          sgeo[r] = geometry(rec);
-          sval[r] = value(cb + r, rec.src);
-        }
+        if (tid < 2) ncount[tid] = 0;
+        __syncthreads();
+        const bool live = cb + tid < end;
+        const int r = live ? cb + tid : cb;
+        const Rec<float> rec = recs[r];
+        fx_put<W>(sgeo, sval, ncount, live, rec, value(r, rec.src), T, beta);
         __syncthreads();
       }
-      fx_pass<RPW, NWAVES>(sgeo, sval, cn, wave, s, splat);
+      const int nw = ncount[0], nh = ncount[1];
+      fx_pass<RPW, NWAVES>(sgeo, sval, nw, wave, s, [&](float4 g, val_t v) { splat(g, v, std::false_type{}); });
+      fx_pass<RPW, NWAVES>(sgeo + (FX_STAGE - nh), sval + (FX_STAGE - nh), nh, wave, s,
+                           [&](float4 g, val_t v) { splat(g, v, std::true_type{}); });
     }
   } else {
     for (int base = beg + wave * RPW; base < end; base += NWAVES * RPW) {
       const int r = base + s;
       if (s < RPW && r < end) {
         const Rec<float> rec = recs[r];
-        splat(geometry(rec), value(r, rec.src));
+        splat(geometry(rec), value(r, rec.src), std::false_type{});
       }
     }
   }
