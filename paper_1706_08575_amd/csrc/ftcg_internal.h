@@ -473,7 +473,9 @@ namespace ftcg {
 // launchers (defined in the .hip files); all enqueue on plan->stream
 constexpr size_t FLAGS_BYTES = 128;       // device flags / pinned host mirror
 constexpr int64_t WROW_CNT_ZERO = 4100;   // bin-row counters cleared by the input check (>= WROW_MAX + 1)
-constexpr int CHECK_PARTS = 1024;         // input-check workgroups at most
+constexpr int CHECK_PARTS = 256;         // input-check workgroups at most: one per CU. Each adds an arrival at
+                                          // one ticket, and the last folds all partials (2^23 points 50 us
+                                          // with 1024 of them, 44 with 256; 2^20 14.9 and 12.4)
 // returns the number of partial records (5 words each) written to part
 void launch_check_points(ftcg_plan p, const double* k, int64_t m, int seq, int32_t* zero_a, int64_t zero_na,
                          int32_t* zero_b, int64_t zero_nb);
