@@ -267,25 +267,27 @@ __global__ __launch_bounds__(BAND_BLOCK, NBK == 1 ? 8 : NBK == 2 ? 6 : 4) void k
     }
 }
 
-// element K of a row of 16 lanes, in every lane of the row
-template <int K>
+// element K of a group of GW lanes (a row of 16, or four), in every lane of the group
+template <int K, int GW>
 __device__ inline double row_bcast(double v) {
+  static_assert(GW == 16 || GW == 4, "DPP broadcasts within a row or a quad");
+  constexpr int CTRL = GW == 16 ? 0x150 + K : K * 0x55;
   const long long b = __builtin_bit_cast(long long, v);
-  const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x150 + K, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x150 + K, 0xf, 0xf, true);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
 }
 
 // Step K of the elimination: every other row loses its entry in column K
 // (columns K + 1 .. and the right-hand side are kept up to date). Row p is in
-// lane p % 16, set p / 16. ok clears when the pivot vanishes.
-template <int K, int NBP, int NS>
+// lane p % GW, set p / GW. ok clears when the pivot vanishes.
+template <int K, int NBP, int NS, int GW>
 __device__ inline void band_step(double (&A)[NS][NBP], double (&y)[NS], double (&ip)[NS], const double (&d0)[NS],
                                  int c, bool& ok) {
-  constexpr int S = K / 16, KL = K % 16;
+  constexpr int S = K / GW, KL = K % GW;
   __builtin_amdgcn_sched_barrier(0);   // the next steps' broadcasts would not fit the registers
-  const double piv = row_bcast<KL>(A[S][K]);
-  ok = ok && piv > 1e-13 * row_bcast<KL>(d0[S]);
+  const double piv = row_bcast<KL, GW>(A[S][K]);
+  ok = ok && piv > 1e-13 * row_bcast<KL, GW>(d0[S]);
   double r = rcp64b(piv);
   r = fma(r, fma(-piv, r, 1.0), r);
   double f[NS];
@@ -297,33 +299,33 @@ __device__ inline void band_step(double (&A)[NS][NBP], double (&y)[NS], double (
   }
 #pragma unroll
   for (int t = K + 1; t < NBP; ++t) {
-    const double e = row_bcast<KL>(A[S][t]);
+    const double e = row_bcast<KL, GW>(A[S][t]);
 #pragma unroll
     for (int s = 0; s < NS; ++s) A[s][t] = fma(-f[s], e, A[s][t]);
   }
-  const double e = row_bcast<KL>(y[S]);
+  const double e = row_bcast<KL, GW>(y[S]);
 #pragma unroll
   for (int s = 0; s < NS; ++s) y[s] = fma(-f[s], e, y[s]);
-  if constexpr (K + 1 < NBP) band_step<K + 1, NBP, NS>(A, y, ip, d0, c, ok);
+  if constexpr (K + 1 < NBP) band_step<K + 1, NBP, NS, GW>(A, y, ip, d0, c, ok);
 }
 
-// Column n of C per group of 16 lanes: the L x L normal matrix of J(n), padded
-// to NBP with the identity, row p in the registers of lane p % 16 (set
-// p / 16), eliminated in place without a back substitution (in lockstep lanes
+// Column n of C per group of GW lanes (16; four for r <= 2): the L x L normal matrix of J(n), padded
+// to NBP with the identity, row p in the registers of lane p % GW (set
+// p / GW), eliminated in place without a back substitution (in lockstep lanes
 // the rows above the pivot cost nothing extra). Pivots are the Cholesky
 // factorisation's (its squared diagonal); one vanishing against the
 // matrix's diagonal entry reports a column without full rank. Measured at 2^17
 // columns, r = 8: 51 us, against 241 us for one thread per column with the
 // triangle in LDS (69 KB per wavefront, two wavefronts per compute unit).
-template <int DIM, int NBP>
+template <int DIM, int NBP, int GW>
 __global__ __launch_bounds__(BAND_BLOCK) void k_band_solve(const double* __restrict__ P,
                                                           const WSample<DIM>* __restrict__ ss,
                                                           const int32_t* __restrict__ inv, int64_t m, int r, double R,
                                                           double* __restrict__ bcol, int* __restrict__ bad) {
-  constexpr int NS = (NBP + 15) / 16;
-  const int c = threadIdx.x & 15;
-  const int64_t n = ((int64_t)blockIdx.x * BAND_BLOCK + threadIdx.x) >> 4;
-  if (n >= m) return;   // whole rows of lanes; no barrier below
+  constexpr int NS = (NBP + GW - 1) / GW;
+  const int c = threadIdx.x % GW;
+  const int64_t n = ((int64_t)blockIdx.x * BAND_BLOCK + threadIdx.x) / GW;
+  if (n >= m) return;   // whole groups of lanes; no barrier below
   const int nb = 2 * r - 1;
   const int64_t lo = std::max<int64_t>(0, n - r + 1), hi = std::min<int64_t>(m - 1, n + r - 1);
   const int L = (int)(hi - lo + 1);
@@ -333,7 +335,7 @@ __global__ __launch_bounds__(BAND_BLOCK) void k_band_solve(const double* __restr
   load_sample<DIM>(ss[inv[n]], x, sn, cs);
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
-    const int p = 16 * s + c;
+    const int p = GW * s + c;
     const bool row = p < L;
 #pragma unroll
     for (int t = 0; t < NBP; ++t) {
@@ -346,13 +348,13 @@ __global__ __launch_bounds__(BAND_BLOCK) void k_band_solve(const double* __restr
     ip[s] = 1.0;
   }
   bool ok = true;
-  band_step<0, NBP, NS>(A, y, ip, d0, c, ok);
+  band_step<0, NBP, NS, GW>(A, y, ip, d0, c, ok);
   if (!ok && c == 0) atomicAdd(bad, 1);
   // the sums carry pi^(2 DIM), the right-hand side pi^DIM: C = pi^DIM x
   constexpr double SC = DIM == 1 ? WPI : WPI * WPI;
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
-    const int p = 16 * s + c;
+    const int p = GW * s + c;
     if (p < L) bcol[n * nb + off + p] = ok ? SC * (y[s] * ip[s]) : 0.0;
     if (p < nb && (p < off || p >= off + L)) bcol[n * nb + p] = 0.0;
   }
@@ -401,6 +403,13 @@ __global__ __launch_bounds__(APPLY_NT) void k_band_apply(const double* __restric
 static int run_blocks(int r) { return r <= 5 ? 1 : r <= 9 ? 2 : 3; }
 static int run_stride(int r) { return std::min(16, 16 * run_blocks(r) - 2 * (r - 1)); }
 
+// Bands of r <= 3 have at most five offsets, which k_band_gram forms in one pass
+// with each T_{i,j} formed at most five times; a run of 12 or 14 samples then
+// gains nothing over its wider box and leaves a good part of the runs to that
+// kernel all the same. 59 515 samples on 448^2, points: r = 2 330 us by runs,
+// 240 without; r = 3 281 and 244; r = 4 203 and 254; r = 5 152 and 412.
+static bool band_by_runs(int r) { return r > 3; }
+
 template <int DIM>
 static void launch_band(ftcg_plan p) {
   const int64_t m = p->m;
@@ -416,22 +425,29 @@ static void launch_band(ftcg_plan p) {
   const int32_t* far = nullptr;
   const int stride = run_stride(r);
   if constexpr (DIM == 2) {
-    const int64_t runs = (m + stride - 1) / stride;
-    p->band_far.ensure(sizeof(int32_t) * runs);
-    const int nbk = run_blocks(r);
-    hipLaunchKernelGGL(nbk == 1 ? k_band_gram_mm<1> : nbk == 2 ? k_band_gram_mm<2> : k_band_gram_mm<3>,
-                       dim3((unsigned)((runs + BAND_BLOCK / 64 - 1) / (BAND_BLOCK / 64))), dim3(BAND_BLOCK), 0, s, ss,
-                       inv, boff, m, p->wgeom, nb, stride, p->band_far.as<int32_t>(), P);
-    far = p->band_far.as<int32_t>();
+    if (band_by_runs(r)) {
+      const int64_t runs = (m + stride - 1) / stride;
+      p->band_far.ensure(sizeof(int32_t) * runs);
+      const int nbk = run_blocks(r);
+      hipLaunchKernelGGL(nbk == 1 ? k_band_gram_mm<1> : nbk == 2 ? k_band_gram_mm<2> : k_band_gram_mm<3>,
+                         dim3((unsigned)((runs + BAND_BLOCK / 64 - 1) / (BAND_BLOCK / 64))), dim3(BAND_BLOCK), 0, s,
+                         ss, inv, boff, m, p->wgeom, nb, stride, p->band_far.as<int32_t>(), P);
+      far = p->band_far.as<int32_t>();
+    }
   }
   hipLaunchKernelGGL((k_band_gram<DIM, BAND_NC>), dim3(gb, (unsigned)((nb + BAND_NC - 1) / BAND_NC)), dim3(BAND_BLOCK),
                      0, s, ss, inv, boff, m, p->wgeom, nb, far, stride, bad, P);
   FTCG_HIP(hipGetLastError());
   timing_end(p, STEP_BAND_GRAM);
   timing_begin(p, STEP_BAND_SOLVE);
-  const unsigned gs = (unsigned)((m * 16 + BAND_BLOCK - 1) / BAND_BLOCK);
-  hipLaunchKernelGGL((r <= 4 ? k_band_solve<DIM, 7> : r <= 8 ? k_band_solve<DIM, 15> : r <= 12 ? k_band_solve<DIM, 23>
-                                                                                     : k_band_solve<DIM, 31>),
+  const int gw = r <= 2 ? 4 : 16;
+  const unsigned gs = (unsigned)((m * gw + BAND_BLOCK - 1) / BAND_BLOCK);
+  hipLaunchKernelGGL((r <= 2    ? k_band_solve<DIM, 3, 4>
+                      : r <= 3  ? k_band_solve<DIM, 5, 16>
+                      : r <= 4  ? k_band_solve<DIM, 7, 16>
+                      : r <= 8  ? k_band_solve<DIM, 15, 16>
+                      : r <= 12 ? k_band_solve<DIM, 23, 16>
+                                : k_band_solve<DIM, 31, 16>),
                      dim3(gs), dim3(BAND_BLOCK), 0, s, P, ss, inv, m, r, p->R, p->band_col.as<double>(), bad);
   FTCG_HIP(hipGetLastError());
   timing_end(p, STEP_BAND_SOLVE);
