@@ -1135,9 +1135,13 @@ void run_plain_weights(ftcg_plan p) {
       p->dim == 2 ? (double)p->m / ((double)g.nb[0] * g.nb[1]) * (2 * g.span + 1) * (2 * g.span + 1) : 0.0;
   // samples per lane: 2 in 2D from 2^20 samples, but 1 when a sample has more
   // than about 10^4 candidates (3.5 M samples on a 256^2 image: 39 against
-  // 41 ms)
-  const int wt = p->w_samples ? p->w_samples
-                              : (p->dim == 2 && p->m >= (int64_t(1) << 20) && cand <= 1e4 ? 2 : 1);
+  // 41 ms); with at most 10^3 candidates already from 600 000 samples, where
+  // the lanes are enough and the shared reciprocal and LDS atomic pay (2 against
+  // 1, four lanes each: 0.62 M samples on 1024^2 134 and 148 us, 0.88 M 232 and
+  // 272, 0.74 M on 2048^2 80 and 87; with 1160 candidates, 0.62 M on 512^2, 528
+  // and 400)
+  const int64_t two = cand <= 1e3 ? 600000 : int64_t(1) << 20;
+  const int wt = p->w_samples ? p->w_samples : (p->dim == 2 && p->m >= two && cand <= 1e4 ? 2 : 1);
   if (p->dim == 2) {
     // lanes per sample group: the plan's tuning, else 4 below 2^21 samples
     // and 2 from there, but 1 when a sample has more than about 10^4
