@@ -497,6 +497,7 @@ void run_plain_weights(ftcg_plan p);                // alpha (caller order) from
 bool small_1d(const ftcg_plan_s* p);                // 1D plain weights and binning in one launch
 void small_1d_points(ftcg_plan p, const double* k, int seq);
 void finish_deferred_weights(ftcg_plan p);          // no-op unless p->weights_deferred
+bool being_captured(const ftcg_plan_s* p);
 // ftcg_set_points in two parts (a batch enqueues every item's first part
 // before the host waits for the first input check); throw on errors
 void set_points_begin(ftcg_plan p, int64_t m, const double* k_dev);

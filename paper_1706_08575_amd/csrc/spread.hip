@@ -1009,12 +1009,7 @@ static void settle_weights(ftcg_plan p) {
     ++p->deferred_spreads;
     return;
   }
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(p->stream, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return;
-  }
-  if (st == hipStreamCaptureStatusNone) finish_deferred_weights(p);
+  if (!being_captured(p)) finish_deferred_weights(p);
 }
 
 template <class real, int W>

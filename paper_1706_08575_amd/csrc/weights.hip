@@ -1100,6 +1100,19 @@ static void launch_weights_1d(ftcg_plan p) {
                      p->ws_idx.as<int32_t>(), p->wb_off.as<int32_t>(), p->m, p->wgeom, p->alpha.as<double>());
 }
 
+// whether the plan's stream records into a graph (also where that is not known)
+bool being_captured(const ftcg_plan_s* p) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(p->stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+// A call being captured only records the finish: what it writes is there once the
+// graph has run, so the weights stay deferred for the next call that is not
+// captured. (It reads the sums alone, so it can run any number of times.)
 void finish_deferred_weights(ftcg_plan p) {
   if (!p->weights_deferred) return;
   timing_begin(p, STEP_WFINISH);
@@ -1117,7 +1130,7 @@ void finish_deferred_weights(ftcg_plan p) {
                        p->recs.as<Rec<float>>(), nrec, p->alpha_s.as<float>());
   FTCG_HIP(hipGetLastError());
   timing_end(p, STEP_WFINISH);
-  p->weights_deferred = false;
+  if (!being_captured(p)) p->weights_deferred = false;
 }
 
 // samples per lane: the plan's tuning, else in 2D 2 from 2^20 samples (each
