@@ -145,7 +145,11 @@ ftcg_status ftcg_get_weights(ftcg_plan plan, double* alpha_dev, int* used_fallba
  *               (complex128 / complex64 by dtype), read only.
  *   image_dev : device, n^dim complex values, row-major, written entirely.
  * FTCG_ESTATE before ftcg_set_points (and, for FTCG_W_USER, the weights);
- * FTCG_EINVAL for NULL pointers. Enqueues only (no host synchronisation). */
+ * FTCG_EINVAL for NULL pointers. Enqueues only (no host synchronisation).
+ * A call captured into a HIP graph reads the plan's buffers when the graph runs:
+ * a replay takes the points and weights the plan has by then. It stays valid
+ * while ftcg_set_points is called with the same number of samples only (other
+ * numbers may move the buffers) and the plan's tuning is not changed. */
 ftcg_status ftcg_execute(ftcg_plan plan, const void* fhat_dev, void* image_dev);
 
 /* Forward (type-2) transform at the plan's raster: the adjoint of the

@@ -124,7 +124,7 @@ void set_points_begin(ftcg_plan p, int64_t m, const double* k_dev) {
   p->have_points = false;
   p->have_weights = false;
   p->finish_recs = false;
-  p->weights_deferred = false;
+  p->weights_deferred = p->sums_ready = false;
   p->deferred_spreads = 0;
   p->alpha_by_src = false;
   p->pending = {};

@@ -409,8 +409,9 @@ struct ftcg_plan_s {
   // spread of one partial tile forms each record's weight from ws_sum itself,
   // and finish_deferred_weights writes alpha and the records' weights when
   // anything else needs them, or when the points have served as many spreads
-  // as settle_weights allows
+  // as from_sums allows
   bool weights_deferred = false;
+  bool sums_ready = false;    // ws_sum and ws_inv give the records' weights of these points, finished or not
   bool alpha_by_src = false;  // the records carry no weights: the 1D spread reads alpha[src]
   int deferred_spreads = 0;   // spreads that formed the weights so far
   ftcg::WBinGeom wgeom{};
@@ -496,7 +497,7 @@ void build_weight_bins_1d(ftcg_plan p, const double* k);   // 1D sorted neighbou
 void run_plain_weights(ftcg_plan p);                // alpha (caller order) from the bins
 bool small_1d(const ftcg_plan_s* p);                // 1D plain weights and binning in one launch
 void small_1d_points(ftcg_plan p, const double* k, int seq);
-void finish_deferred_weights(ftcg_plan p);          // no-op unless p->weights_deferred
+void finish_deferred_weights(ftcg_plan p);          // no-op unless they are deferred or the call is captured
 bool being_captured(const ftcg_plan_s* p);
 // ftcg_set_points in two parts (a batch enqueues every item's first part
 // before the host waits for the first input check); throw on errors

@@ -935,8 +935,8 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread1d(const Rec<real>* __re
 }
 
 template <int W, int T>
-static void launch_fx(ftcg_plan p, const void* fhat, void* grid) {
-  if (p->weights_deferred)
+static void launch_fx(ftcg_plan p, const void* fhat, void* grid, bool sums) {
+  if (sums)
     hipLaunchKernelGGL((k_spread2d_fx<W, T, FX_SUMS>), dim3((unsigned)p->ntiles), dim3(SPREAD_BLOCK), 0, p->stream,
                        p->recs.as<Rec<float>>(), p->alpha_s.as<float>(), p->ws_sum.as<double>(),
                        p->ws_inv.as<int32_t>(), p->tile_off.as<int32_t>(), static_cast<const float2*>(fhat),
@@ -960,9 +960,9 @@ static int spread_segment_rows(const ftcg_plan_s* p) {
 }
 
 template <int W>
-static void launch_seg(ftcg_plan p, const void* fhat, void* grid, int K) {
+static void launch_seg(ftcg_plan p, const void* fhat, void* grid, int K, bool sums) {
   const unsigned nb = (unsigned)((p->nt / SEG_CW) * (p->nt / K));
-  if (p->weights_deferred)
+  if (sums)
     hipLaunchKernelGGL((k_spread2d_seg<W, true>), dim3(nb), dim3(SEG_BLOCK), 0, p->stream, p->recs.as<Rec<float>>(),
                        p->alpha_s.as<float>(), p->ws_sum.as<double>(), p->ws_inv.as<int32_t>(),
                        p->tile_off.as<int32_t>(), static_cast<const float2*>(fhat), static_cast<float2*>(grid), p->G,
@@ -975,20 +975,20 @@ static void launch_seg(ftcg_plan p, const void* fhat, void* grid, int K) {
 }
 
 template <int W>
-static void launch_fx_t(ftcg_plan p, const void* fhat, void* grid) {
+static void launch_fx_t(ftcg_plan p, const void* fhat, void* grid, bool sums) {
   if (p->spread_segments) {
     const int K = spread_segment_rows(p);
     if (K > 0) {
-      launch_seg<W>(p, fhat, grid, K);
+      launch_seg<W>(p, fhat, grid, K, sums);
       FTCG_HIP(hipGetLastError());
       return;
     }
   }
   switch (p->tile) {
-    case 16: launch_fx<W, 16>(p, fhat, grid); break;
-    case 32: launch_fx<W, 32>(p, fhat, grid); break;
-    case 64: launch_fx<W, 64>(p, fhat, grid); break;
-    case 128: launch_fx<W, 128>(p, fhat, grid); break;
+    case 16: launch_fx<W, 16>(p, fhat, grid, sums); break;
+    case 32: launch_fx<W, 32>(p, fhat, grid, sums); break;
+    case 64: launch_fx<W, 64>(p, fhat, grid, sums); break;
+    case 128: launch_fx<W, 128>(p, fhat, grid, sums); break;
     default: throw StatusError{FTCG_EUNSUPPORTED};
   }
   FTCG_HIP(hipGetLastError());
@@ -1000,31 +1000,34 @@ static void launch_fx_t(ftcg_plan p, const void* fhat, void* grid) {
 // records' weights. The finish costs about two such spreads' extra (1M samples
 // on 1024^2: 18 us against 8 a spread, 128 and 120 us a call; 756k in float64
 // 18 against 10, 160 and 150), so the third takes it. A call being captured
-// leaves the plan as it is, because what it records has not run when the next
-// call reads the weights.
+// always forms them: points set before a replay refresh the sums, and not the
+// records' weights.
 constexpr int DEFERRED_SPREADS = 2;
-static void settle_weights(ftcg_plan p) {
-  if (!p->weights_deferred) return;
+static bool from_sums(ftcg_plan p) {
+  if (!p->sums_ready) return false;
+  if (being_captured(p)) return true;
+  if (!p->weights_deferred) return false;
   if (p->deferred_spreads < DEFERRED_SPREADS) {
     ++p->deferred_spreads;
-    return;
+    return true;
   }
-  if (!being_captured(p)) finish_deferred_weights(p);
+  finish_deferred_weights(p);
+  return false;
 }
 
 template <class real, int W>
 static void launch_spread_w(ftcg_plan p, const void* fhat, void* grid) {
   using cx = typename Cx<real>::t;
   const int T = p->tile;
-  settle_weights(p);
+  const bool sums = from_sums(p);
   if (std::is_same<real, float>::value && p->dim == 2 && p->accum == ACCUM_FIXED) {
-    launch_fx_t<W>(p, fhat, grid);   // forms deferred weights itself
+    launch_fx_t<W>(p, fhat, grid, sums);
     return;
   }
-  if (p->dim == 2 && p->weights_deferred &&
+  if (p->dim == 2 && sums &&
       launch_mm<real, W, FX_SUMS>(p, static_cast<const cx*>(fhat), static_cast<cx*>(grid)))
     return;
-  finish_deferred_weights(p);          // the other kernels read the records' weights
+  if (sums) finish_deferred_weights(p);   // the other kernels read the records' weights
   const real beta = (real)p->beta;
   const int copies = p->lds_copies;
   if (p->dim == 2) {

@@ -1073,7 +1073,7 @@ static void launch_weights_sym(ftcg_plan p) {
                      p->ws_k.as<WSample<2>>(), p->wb_off.as<int32_t>(), g, cx, chunk, wsum);
   timing_end(p, STEP_WEIGHTS);
   if (p->finish_recs) {   // finished on demand (finish_deferred_weights) or inside the spread
-    p->weights_deferred = true;
+    p->weights_deferred = p->sums_ready = true;
     p->finish_recs = false;
     return;
   }
@@ -1112,9 +1112,13 @@ bool being_captured(const ftcg_plan_s* p) {
 
 // A call being captured only records the finish: what it writes is there once the
 // graph has run, so the weights stay deferred for the next call that is not
-// captured. (It reads the sums alone, so it can run any number of times.)
+// captured. It is recorded although the weights may be finished already (it reads
+// the sums alone and can run any number of times): a replay then also takes the
+// sums of points set since, which leave the records' weights to a finish.
 void finish_deferred_weights(ftcg_plan p) {
-  if (!p->weights_deferred) return;
+  if (!p->sums_ready) return;
+  const bool captured = being_captured(p);
+  if (!p->weights_deferred && !captured) return;
   timing_begin(p, STEP_WFINISH);
   const int64_t m = p->m;
   const double* wsum = p->ws_sum.as<double>();
@@ -1130,7 +1134,7 @@ void finish_deferred_weights(ftcg_plan p) {
                        p->recs.as<Rec<float>>(), nrec, p->alpha_s.as<float>());
   FTCG_HIP(hipGetLastError());
   timing_end(p, STEP_WFINISH);
-  if (!being_captured(p)) p->weights_deferred = false;
+  if (!captured) p->weights_deferred = false;
 }
 
 // samples per lane: the plan's tuning, else in 2D 2 from 2^20 samples (each

@@ -1,5 +1,6 @@
 """Calls captured into a graph: a capture only records, so it leaves the plan's
-weights as they were.
+weights as they were, and a replay takes the points the plan has by then (the same
+number of samples, so that no buffer moves).
 
 Float32 plans add integers, so equal points give equal images bit for bit;
 float64 accumulation adds in any order: 1e-12 relative in float64, 1e-6 where the
@@ -50,6 +51,38 @@ def fresh(dtype, tuning, k, f, dim=2, n=N):
         img = P.execute(f.to(P.cdtype))
         torch.cuda.synchronize()
         return img, w
+
+
+@pytest.mark.parametrize("dtype,tuning", SUMS + RECORDS)
+@pytest.mark.parametrize("before", [0, 2, 4])
+def test_replay_takes_new_points(dtype, tuning, before):
+    k1, f1 = raster(11)
+    k2, f2 = raster(12)
+    ref1, _ = fresh(dtype, tuning, k1, f1)
+    ref2, w2 = fresh(dtype, tuning, k2, f2)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s), plan(dtype, tuning, stream=s) as P:
+        P.set_points(k1)
+        f = f1.to(P.cdtype)
+        for _ in range(before):
+            P.execute(f)
+        out = torch.zeros_like(ref1)
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            P.execute(f, out=out)
+        g.replay()
+        s.synchronize()
+        assert same(out, ref1, dtype, tuning)
+        P.set_points(k2)
+        f.copy_(f2)
+        for _ in range(3):
+            out.zero_()
+            g.replay()
+            s.synchronize()
+            assert same(out, ref2, dtype, tuning)
+            assert same(P.execute(f), ref2, dtype, tuning)
+        assert torch.equal(P.get_weights(), w2)
 
 
 @pytest.mark.parametrize("dtype,tuning", SUMS + RECORDS)
