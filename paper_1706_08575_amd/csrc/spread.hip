@@ -1044,9 +1044,12 @@ static void launch_spread_w(ftcg_plan p, const void* fhat, void* grid) {
                        static_cast<const cx*>(fhat), static_cast<cx*>(grid), p->G, (int)p->nt, T, copies, beta);
   } else {
     const size_t lds = (size_t)copies * 2 * T * sizeof(double);
+    // a captured call takes the caller-order weights, which every path of
+    // set_points writes, so that a replay finds those of whichever it was
+    const bool by_src = p->alpha_by_src || (p->wmode == FTCG_W_PLAIN && being_captured(p));
     hipLaunchKernelGGL((k_spread1d<real, W>), dim3((unsigned)p->ntiles), dim3(SPREAD_BLOCK), lds, p->stream,
                        p->recs.as<Rec<real>>(), p->alpha_s.as<real>(),
-                       p->alpha_by_src ? p->alpha.as<double>() : nullptr, p->tile_off.as<int32_t>(),
+                       by_src ? p->alpha.as<double>() : nullptr, p->tile_off.as<int32_t>(),
                        static_cast<const cx*>(fhat), static_cast<cx*>(grid), T, copies, beta);
   }
   FTCG_HIP(hipGetLastError());
