@@ -27,6 +27,7 @@ static hipEvent_t take_event(Timing& t) {
 void timing_begin(ftcg_plan p, int step) {
   Timing& t = p->timing;
   if (!t.enabled) return;
+  if (t.open_ev) t.pool.push_back(t.open_ev);   // a step that ended in an error
   t.open_ev = take_event(t);
   t.open_step = step;
   FTCG_HIP(hipEventRecord(t.open_ev, p->stream));
@@ -455,8 +456,9 @@ ftcg_status ftcg_spread_only(ftcg_plan p, const void* fhat_dev, void* grid_dev) 
       band_apply(p, fhat_dev);
       fhat_dev = p->band_c.p;
     }
+    const bool sums = ready_weights(p);
     timing_begin(p, STEP_SPREAD);
-    spread(p, fhat_dev, grid_dev);
+    spread(p, fhat_dev, grid_dev, sums);
     timing_end(p, STEP_SPREAD);
   });
 }
@@ -474,8 +476,9 @@ ftcg_status ftcg_execute(ftcg_plan p, const void* fhat_dev, void* image_dev) {
       band_apply(p, fhat_dev);
       fhat_dev = p->band_c.p;
     }
+    const bool sums = ready_weights(p);
     timing_begin(p, STEP_SPREAD);
-    spread(p, fhat_dev, p->grid.p);
+    spread(p, fhat_dev, p->grid.p, sums);
     timing_end(p, STEP_SPREAD);
     grid_to_image(p, p->grid.p, image_dev);
   });

@@ -68,7 +68,7 @@ static void run_density_t(ftcg_plan p) {
   one.y = 0;
   hipLaunchKernelGGL(k_den_init<cx>, dim3(gb), dim3(DEN_BLOCK), 0, p->stream, w, val, one, m);
   for (int it = 0; it < p->den_iters; ++it) {
-    spread(p, val, p->grid.p);
+    spread(p, val, p->grid.p, false);
     interpolate_grid(p, den);
     hipLaunchKernelGGL(k_den_update<cx>, dim3(gb), dim3(DEN_BLOCK), 0, p->stream, w, den, val, m, scale,
                        it + 1 == p->den_iters ? 1 : 0);

@@ -409,7 +409,7 @@ struct ftcg_plan_s {
   // spread of one partial tile forms each record's weight from ws_sum itself,
   // and finish_deferred_weights writes alpha and the records' weights when
   // anything else needs them, or when the points have served as many spreads
-  // as from_sums allows
+  // as ready_weights allows
   bool weights_deferred = false;
   bool sums_ready = false;    // ws_sum and ws_inv give the records' weights of these points, finished or not
   bool alpha_by_src = false;  // the records carry no weights: the 1D spread reads alpha[src]
@@ -523,7 +523,10 @@ void interpolate_density(ftcg_plan p, double* w, void* val, double scale, bool l
 void run_density_weights(ftcg_plan p);              // iterative density compensation into p->alpha
 // dense frame approximation of the raster k (m samples) into image (float64 plans)
 void frame_approx(ftcg_plan p, int64_t m, const double* k, const void* fhat, void* image);
-void spread(ftcg_plan p, const void* fhat, void* grid);
+// before a spread, outside its timed step: finishes the weights where this spread needs
+// them finished; true when it forms them from the sums itself
+bool ready_weights(ftcg_plan p);
+void spread(ftcg_plan p, const void* fhat, void* grid, bool sums);
 void grid_to_image(ftcg_plan p, const void* grid, void* image);
 void compute_deapod(ftcg_plan p);
 void compute_deapod_raw(double* d, int64_t n, double sigma, double beta, hipStream_t s);

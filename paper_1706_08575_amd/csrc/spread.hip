@@ -257,25 +257,26 @@ __global__ __launch_bounds__(64 * MmTile<T>::NW, T == 64 ? 3 : 6) void k_spread2
   }
 }
 
-// true when the kernel above took the launch: one partial tile of 32 or 64
-// cells. At 16 a block is the whole tile: one wavefront per workgroup and 19 KiB
-// of LDS leave too few of them, and the LDS-atomic kernel stays.
+// plans whose float64 accumulation runs through the kernel above: one partial tile
+// of 32 or 64 cells. At 16 a block is the whole tile: one wavefront per workgroup and
+// 19 KiB of LDS leave too few of them, and the LDS-atomic kernel stays.
+static bool spreads_by_products(const ftcg_plan_s* p) {
+  return p->dim == 2 && p->lds_copies == 1 && (p->tile == 32 || p->tile == 64);
+}
+
 template <class real, int W, int SRC, class Val>
-static bool launch_mm(ftcg_plan p, const Val* val, Val* grid) {
-  if (p->lds_copies != 1) return false;
+static void launch_mm(ftcg_plan p, const Val* val, Val* grid) {
   auto go = [&](auto kernel, int nw) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)p->ntiles), dim3(64 * nw), 0, p->stream, p->recs.as<Rec<real>>(),
                        p->alpha_s.as<real>(), p->ws_sum.as<double>(), p->ws_inv.as<int32_t>(),
                        p->tile_off.as<int32_t>(), val, grid, p->G, (int)p->nt, (real)p->beta,
                        (real)std::exp(-2 * p->beta));
-    FTCG_HIP(hipGetLastError());
-    return true;
   };
-  switch (p->tile) {
-    case 32: return go(k_spread2d_mm<real, W, 32, SRC>, MmTile<32>::NW);
-    case 64: return go(k_spread2d_mm<real, W, 64, SRC>, MmTile<64>::NW);
-    default: return false;
-  }
+  if (p->tile == 32)
+    go(k_spread2d_mm<real, W, 32, SRC>, MmTile<32>::NW);
+  else
+    go(k_spread2d_mm<real, W, 64, SRC>, MmTile<64>::NW);
+  FTCG_HIP(hipGetLastError());
 }
 
 // REAL: weight 1, real values and a real grid (the density iterations): one
@@ -1003,35 +1004,39 @@ static void launch_fx_t(ftcg_plan p, const void* fhat, void* grid, bool sums) {
 // always forms them: points set before a replay refresh the sums, and not the
 // records' weights.
 constexpr int DEFERRED_SPREADS = 2;
-static bool from_sums(ftcg_plan p) {
+bool ready_weights(ftcg_plan p) {
   if (!p->sums_ready) return false;
-  if (being_captured(p)) return true;
-  if (!p->weights_deferred) return false;
-  if (p->deferred_spreads < DEFERRED_SPREADS) {
-    ++p->deferred_spreads;
-    return true;
+  const bool forms = p->dim == 2 && (p->accum == ACCUM_FIXED || spreads_by_products(p));
+  if (forms) {
+    if (being_captured(p)) return true;
+    if (!p->weights_deferred) return false;
+    if (p->deferred_spreads < DEFERRED_SPREADS) {
+      ++p->deferred_spreads;
+      return true;
+    }
   }
   finish_deferred_weights(p);
   return false;
 }
 
 template <class real, int W>
-static void launch_spread_w(ftcg_plan p, const void* fhat, void* grid) {
+static void launch_spread_w(ftcg_plan p, const void* fhat, void* grid, bool sums) {
   using cx = typename Cx<real>::t;
   const int T = p->tile;
-  const bool sums = from_sums(p);
   if (std::is_same<real, float>::value && p->dim == 2 && p->accum == ACCUM_FIXED) {
     launch_fx_t<W>(p, fhat, grid, sums);
     return;
   }
-  if (p->dim == 2 && sums &&
-      launch_mm<real, W, FX_SUMS>(p, static_cast<const cx*>(fhat), static_cast<cx*>(grid)))
-    return;
-  if (sums) finish_deferred_weights(p);   // the other kernels read the records' weights
   const real beta = (real)p->beta;
   const int copies = p->lds_copies;
   if (p->dim == 2) {
-    if (launch_mm<real, W, FX_RECS>(p, static_cast<const cx*>(fhat), static_cast<cx*>(grid))) return;
+    if (spreads_by_products(p)) {
+      if (sums)
+        launch_mm<real, W, FX_SUMS>(p, static_cast<const cx*>(fhat), static_cast<cx*>(grid));
+      else
+        launch_mm<real, W, FX_RECS>(p, static_cast<const cx*>(fhat), static_cast<cx*>(grid));
+      return;
+    }
     const size_t lds = (size_t)copies * 2 * T * (T + 1) * sizeof(double);
     static bool attr_done = false;
     if (!attr_done) {
@@ -1079,7 +1084,10 @@ static void launch_spread_real(ftcg_plan p, const void* val, void* grid) {
       return;
     }
   }
-  if (launch_mm<real, W, FX_REAL>(p, static_cast<const real*>(val), static_cast<real*>(grid))) return;
+  if (spreads_by_products(p)) {
+    launch_mm<real, W, FX_REAL>(p, static_cast<const real*>(val), static_cast<real*>(grid));
+    return;
+  }
   const int copies = p->lds_copies;
   const size_t lds = (size_t)copies * T * (T + 1) * sizeof(double);
   FTCG_HIP(hipFuncSetAttribute((const void*)k_spread2d<real, W, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1119,24 +1127,24 @@ void spread_real(ftcg_plan p, const void* val, void* grid) {
 }
 
 template <class real>
-static void launch_spread_t(ftcg_plan p, const void* fhat, void* grid) {
+static void launch_spread_t(ftcg_plan p, const void* fhat, void* grid, bool sums) {
   switch (p->W) {
-    case 2: launch_spread_w<real, 2>(p, fhat, grid); break;
-    case 3: launch_spread_w<real, 3>(p, fhat, grid); break;
-    case 4: launch_spread_w<real, 4>(p, fhat, grid); break;
-    case 5: launch_spread_w<real, 5>(p, fhat, grid); break;
-    case 6: launch_spread_w<real, 6>(p, fhat, grid); break;
-    case 7: launch_spread_w<real, 7>(p, fhat, grid); break;
-    case 8: launch_spread_w<real, 8>(p, fhat, grid); break;
+    case 2: launch_spread_w<real, 2>(p, fhat, grid, sums); break;
+    case 3: launch_spread_w<real, 3>(p, fhat, grid, sums); break;
+    case 4: launch_spread_w<real, 4>(p, fhat, grid, sums); break;
+    case 5: launch_spread_w<real, 5>(p, fhat, grid, sums); break;
+    case 6: launch_spread_w<real, 6>(p, fhat, grid, sums); break;
+    case 7: launch_spread_w<real, 7>(p, fhat, grid, sums); break;
+    case 8: launch_spread_w<real, 8>(p, fhat, grid, sums); break;
     default: throw StatusError{FTCG_EUNSUPPORTED};
   }
 }
 
-void spread(ftcg_plan p, const void* fhat, void* grid) {
+void spread(ftcg_plan p, const void* fhat, void* grid, bool sums) {
   if (p->dtype == FTCG_F64)
-    launch_spread_t<double>(p, fhat, grid);
+    launch_spread_t<double>(p, fhat, grid, sums);
   else
-    launch_spread_t<float>(p, fhat, grid);
+    launch_spread_t<float>(p, fhat, grid, sums);
 }
 
 }  // namespace ftcg
