@@ -266,7 +266,10 @@ ftcg_status ftcg_plan_info(ftcg_plan plan, int64_t* grid_size, int64_t* n_record
  *                      accumulated exactly as packed int32 (re, im) pairs with
  *                      one 64-bit LDS integer add per tap; results are bitwise
  *                      reproducible, error <= half of 2^-31 of the tile bound
- *                      per tap (unbiased).
+ *                      per tap (unbiased). The bound sums over the tile's
+ *                      records, so a larger tile of a dense raster has a coarser
+ *                      quantum (54 samples per pixel: 4.5e-6 relative L2 of the
+ *                      image at tile 32, 1.3e-5 at 64).
  *   FTCG_ACCUM_F64   : taps accumulated with float64 LDS atomics (the default
  *                      and only mode of float64 plans); lds_copies > 1 gives
  *                      each wavefront its own partial tile, combined at the
@@ -426,9 +429,10 @@ ftcg_status ftcg_batch_create(ftcg_batch* out, int n_items, const int64_t* n_hos
                               double oversampling, ftcg_wmode wmode, double weight_radius, void* hip_stream);
 ftcg_status ftcg_batch_destroy(ftcg_batch batch);
 
-/* tile edge (16/32/64/128, default 32), records per task (>= 64, default
- * 4096), workgroups of the persistent launch (default 8 per CU), graph replay
- * on/off (default on). The points must be set again afterwards. */
+/* tile edge (16/32/64/128, default 32; larger ones have a coarser quantum, see
+ * FTCG_ACCUM_FIXED), records per task (>= 64, default 4096), workgroups of the
+ * persistent launch (default 8 per CU), graph replay on/off (default on). The
+ * points must be set again afterwards. */
 ftcg_status ftcg_batch_set_tuning(ftcg_batch batch, int tile, int64_t chunk_records, int persistent_blocks,
                                   int use_graph);
 
