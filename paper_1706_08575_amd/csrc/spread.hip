@@ -442,7 +442,10 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
     else
       return make_float2(v.x * a, v.y * a);
   };
-  // its larger |component|; NaN and infinities give infinity
+  // its larger |component|; NaN and infinities give infinity. (& and not &&: behind
+  // a branch the second component was loaded after the first had been tested, two
+  // trips to memory a record in both passes below. 2^22 random samples on 1024^2:
+  // 414 and 376 us at W = 6, 270 and 230 at W = 2.)
   auto size_of = [](val_t v) -> float {
     float m, t;
     if constexpr (REAL) {
@@ -451,7 +454,7 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
       m = fabsf(v.x);
       t = fabsf(v.y);
     }
-    return (isfinite(m) && isfinite(t)) ? fmaxf(m, t) : __builtin_inff();
+    return (isfinite(m) & isfinite(t)) ? fmaxf(m, t) : __builtin_inff();
   };
   auto geometry = [&](const Rec<float>& rec) -> float4 {
     const float d0 = (float)(1 - W) - rec.f0;
