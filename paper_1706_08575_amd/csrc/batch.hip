@@ -105,6 +105,7 @@ __global__ __launch_bounds__(BATCH_BLOCK) void k_spread_persistent(const BatchTa
   // records staged as in the single-plan kernel, while they fit 64 KiB with the tile
   constexpr bool STAGED = ROWS * TP * 8 + FX_STAGE * 24 <= 64 * 1024;
   constexpr int STG = STAGED ? FX_STAGE : 1;
+  constexpr bool HALF = fx_halves(W, T);
   __shared__ unsigned long long acc[ROWS * TP];
   __shared__ float4 sgeo[STG];   // f1, first row's kernel value, ratio of the rows, c01 (bits)
   __shared__ float2 sval[STG];   // alpha * fhat
@@ -160,17 +161,16 @@ __global__ __launch_bounds__(BATCH_BLOCK) void k_spread_persistent(const BatchTa
       static_assert(FX_STAGE == BATCH_BLOCK, "one staged record per thread");
       for (int cb = tk.beg; cb < tk.end; cb += FX_STAGE) {
         if (cb != tk.beg) __syncthreads();   // every wavefront has left the previous chunk
-        if (tid < 2) ncount[tid] = 0;
-        __syncthreads();
+        if constexpr (HALF) {
+          if (tid < 2) ncount[tid] = 0;
+          __syncthreads();
+        }
         const bool live = cb + tid < tk.end;
         const int r = live ? cb + tid : cb;
         const Rec<float> rec = it.recs[r];
-        fx_put<W>(sgeo, sval, ncount, live, rec, value(r, rec.src), T, beta);
+        fx_put<W, HALF>(sgeo, sval, ncount, live, rec, value(r, rec.src), T, beta);
         __syncthreads();
-        const int nw = ncount[0], nh = ncount[1];
-        fx_pass<RPW, NWAVES>(sgeo, sval, nw, wave, s, [&](float4 g, float2 v) { splat(g, v, std::false_type{}); });
-        fx_pass<RPW, NWAVES>(sgeo + (FX_STAGE - nh), sval + (FX_STAGE - nh), nh, wave, s,
-                             [&](float4 g, float2 v) { splat(g, v, std::true_type{}); });
+        fx_chunk<RPW, NWAVES, HALF>(sgeo, sval, ncount, min(tk.end - cb, FX_STAGE), wave, s, splat);
       }
     } else {
       for (int base = tk.beg + wave * RPW; base < tk.end; base += NWAVES * RPW) {

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/ftcg.h"
@@ -187,8 +188,17 @@ __device__ inline void fx_column(unsigned* dst, int pitch, float p, float q, flo
 // samples: 0.73 -> 0.59 ms; on small grids the LDS atomics bound the loop).
 constexpr int FX_STAGE = 256;   // 6 KiB: keeps 7 workgroups of tile 32, W = 6 per CU
 
+// Whether a tile's records are listed in two halves (fx_put): the rows left out
+// have to pay for the counting and for the chunk's second, partly filled pass,
+// and their share grows with W against the tile. us with the lists and without:
+// tile 16, a million samples of a sector on 1024^2, W = 3 43 and 41, W = 6 106 and
+// 115; tile 32, there, W = 4 51 and 56, W = 6 95 and 102, but half a million on
+// 256^2 W = 2 48 and 40, W = 4 97 and 83, W = 6 181 and 181; tile 64, there, W = 2
+// 150 and 118, W = 8 785 and 760.
+constexpr bool fx_halves(int W, int T) { return T == 16 ? W >= 4 : T == 32 && W >= 5; }
+
 // Puts a workgroup's records into the stage, one per thread (live: the thread has
-// one; every thread of a wavefront calls). A record with more than W of its 2W
+// one; every thread of a wavefront calls). HALF: a record with more than W of its 2W
 // rows inside the tile (0 .. T) goes to the front, with all its rows; one with W
 // or fewer (a quarter of them at tile 32, W = 6) to the back, with the W rows that
 // cover those, its factors and row shifted to the first of them. ncount: staged
@@ -197,24 +207,27 @@ constexpr int FX_STAGE = 256;   // 6 KiB: keeps 7 workgroups of tile 32, W = 6 p
 // Without the lists every record walks 2W rows, those outside into halo rows that
 // are dropped: 1M samples on 1024^2 104 -> 96 us (records' weights), 2^17 on 512^2
 // 20.9 -> 20.4.
-template <int W, class Val>
+template <int W, bool HALF, class Val>
 __device__ inline void fx_put(float4* sgeo, Val* sval, int* ncount, bool live, const Rec<float>& rec, Val v, int T,
                               float beta) {
   const int lane = threadIdx.x & 63;
   const int c0 = (int)(int16_t)(rec.c01 & 0xffff), r0 = c0 - W + 1;
-  const bool top = r0 + W <= 0, half = top || T - r0 <= W;
-  const unsigned long long bw = __ballot(live && !half), bh = __ballot(live && half);
-  int basew = 0, baseh = 0;
-  if (lane == 0) {
-    if (bw) basew = atomicAdd(&ncount[0], __popcll(bw));
-    if (bh) baseh = atomicAdd(&ncount[1], __popcll(bh));
+  int slot = threadIdx.x, shift = 0;
+  if constexpr (HALF) {
+    const bool top = r0 + W <= 0, half = top || T - r0 <= W;
+    const unsigned long long bw = __ballot(live && !half), bh = __ballot(live && half);
+    int basew = 0, baseh = 0;
+    if (lane == 0) {
+      if (bw) basew = atomicAdd(&ncount[0], __popcll(bw));
+      if (bh) baseh = atomicAdd(&ncount[1], __popcll(bh));
+    }
+    basew = __shfl(basew, 0);
+    baseh = __shfl(baseh, 0);
+    const int rank = __popcll((half ? bh : bw) & ((1ull << lane) - 1ull));
+    slot = half ? FX_STAGE - 1 - (baseh + rank) : basew + rank;
+    shift = top ? W : 0;
   }
-  basew = __shfl(basew, 0);
-  baseh = __shfl(baseh, 0);
   if (!live) return;
-  const int rank = __popcll((half ? bh : bw) & ((1ull << lane) - 1ull));
-  const int slot = half ? FX_STAGE - 1 - (baseh + rank) : basew + rank;
-  const int shift = top ? W : 0;
   const float d0 = (float)(1 - W + shift) - rec.f0;
   sgeo[slot] = make_float4(rec.f1, fx_row0(d0, beta), fx_ratio(d0, beta),
                            __int_as_float((int)(((uint32_t)rec.c01 & 0xffff0000u) | ((uint32_t)(c0 + shift) & 0xffffu))));
@@ -248,6 +261,22 @@ __device__ inline void fx_pass(const float4* sgeo, const Val* sval, int n, int w
     geo = sgeo[min(r, n - 1)];
     v = sval[min(r, n - 1)];
     if (use) splat(g, c);
+  }
+}
+
+// Taps of one staged chunk of n records: all of them, or (HALF) the whole ones
+// from the front and the halves from the back
+template <int RPW, int NWAVES, bool HALF, class Val, class Splat>
+__device__ inline void fx_chunk(const float4* sgeo, const Val* sval, const int* ncount, int n, int wave, int s,
+                                Splat splat) {
+  auto whole = [&](float4 g, Val v) { splat(g, v, std::false_type{}); };
+  if constexpr (HALF) {
+    const int nw = ncount[0], nh = ncount[1];
+    fx_pass<RPW, NWAVES>(sgeo, sval, nw, wave, s, whole);
+    fx_pass<RPW, NWAVES>(sgeo + (FX_STAGE - nh), sval + (FX_STAGE - nh), nh, wave, s,
+                         [&](float4 g, Val v) { splat(g, v, std::true_type{}); });
+  } else {
+    fx_pass<RPW, NWAVES>(sgeo, sval, n, wave, s, whole);
   }
 }
 

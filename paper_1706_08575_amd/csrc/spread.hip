@@ -467,6 +467,7 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
   // stage only while the tile and the stage fit 64 KiB of LDS together
   constexpr bool STAGED = ROWS * TP * 8 + FX_STAGE * 24 <= 64 * 1024;
   constexpr int STG = STAGED ? FX_STAGE : 1;
+  constexpr bool HALF = fx_halves(W, T);
   __shared__ cell_t acc[ROWS * TP];
   __shared__ float4 sgeo[STG];          // f1, first row's kernel value, ratio of the rows, c01 (bits)
   __shared__ val_t sval[STG];           // alpha * fhat[src]
@@ -494,13 +495,15 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
   val_t mine = {};   // of the staged record of this thread
   if constexpr (STAGED) {
     static_assert(FX_STAGE == SPREAD_BLOCK, "one staged record per thread");
-    if (tid < 2) ncount[tid] = 0;
-    __syncthreads();
+    if constexpr (HALF) {
+      if (tid < 2) ncount[tid] = 0;
+      __syncthreads();
+    }
     const bool live = tid < first;
     const int r = beg + (live ? tid : 0);
     const Rec<float> rec = recs[r];
     mine = value(r, rec.src);
-    fx_put<W>(sgeo, sval, ncount, live, rec, mine, T, beta);
+    fx_put<W, HALF>(sgeo, sval, ncount, live, rec, mine, T, beta);
     if (live) mx = size_of(mine);
   }
   for (int r = beg + first + tid; r < end; r += SPREAD_BLOCK) mx = fmaxf(mx, size_of(value(r, recs[r].src)));
@@ -559,18 +562,17 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
     for (int cb = beg; cb < end; cb += FX_STAGE) {
       if (cb != beg) {   // later chunks: restage once every wavefront has left the previous one
         __syncthreads();
-        if (tid < 2) ncount[tid] = 0;
-        __syncthreads();
+        if constexpr (HALF) {
+          if (tid < 2) ncount[tid] = 0;
+          __syncthreads();
+        }
         const bool live = cb + tid < end;
         const int r = live ? cb + tid : cb;
         const Rec<float> rec = recs[r];
-        fx_put<W>(sgeo, sval, ncount, live, rec, value(r, rec.src), T, beta);
+        fx_put<W, HALF>(sgeo, sval, ncount, live, rec, value(r, rec.src), T, beta);
         __syncthreads();
       }
-      const int nw = ncount[0], nh = ncount[1];
-      fx_pass<RPW, NWAVES>(sgeo, sval, nw, wave, s, [&](float4 g, val_t v) { splat(g, v, std::false_type{}); });
-      fx_pass<RPW, NWAVES>(sgeo + (FX_STAGE - nh), sval + (FX_STAGE - nh), nh, wave, s,
-                           [&](float4 g, val_t v) { splat(g, v, std::true_type{}); });
+      fx_chunk<RPW, NWAVES, HALF>(sgeo, sval, ncount, min(end - cb, FX_STAGE), wave, s, splat);
     }
   } else {
     for (int base = beg + wave * RPW; base < end; base += NWAVES * RPW) {
