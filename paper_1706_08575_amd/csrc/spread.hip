@@ -454,7 +454,7 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d_fx(const Rec<float>* 
       m = fabsf(v.x);
       t = fabsf(v.y);
     }
-    return (isfinite(m) & isfinite(t)) ? fmaxf(m, t) : __builtin_inff();
+    return ((int)isfinite(m) & (int)isfinite(t)) ? fmaxf(m, t) : __builtin_inff();
   };
   auto geometry = [&](const Rec<float>& rec) -> float4 {
     const float d0 = (float)(1 - W) - rec.f0;
