@@ -161,6 +161,48 @@ struct DenOut {
   }
 };
 
+// A square's window of the grid in LDS: ST + 2W - 1 rows, and columns from a multiple
+// of 16 bytes on, so that it is read in 16-byte pieces (none straddles the
+// grid's edge). Its rows are an odd number of pieces apart, so that one column's
+// cells fall on many banks: the samples of a pulse run down a column, and with the
+// plain width, a multiple of 8 or 16 cells at W = 4 and 8, the listed kernel found
+// only 4 or 2 slots there (float32, 2^20 samples on 512^2: W = 8 240 and 125 us, W =
+// 4 71 and 59, W = 6 97 and 88).
+template <class elem, int W, int ST>
+struct Window {
+  static constexpr int EP = 16 / (int)sizeof(elem);
+  static constexpr int LP = (W - 1 + EP - 1) / EP * EP;           // cells left of the square
+  static constexpr int WR = ST + 2 * W - 1, WS = (LP + ST + W + EP - 1) / EP * EP;
+  static constexpr int PITCH = WS + (WS / EP % 2 == 0 ? EP : 0);
+  struct alignas(16) Piece {
+    elem e[EP];
+  };
+  // square (sr, sc) of the G x G grid; indices modulo G
+  __device__ static void load(elem* win, const elem* __restrict__ grid, int G, int sr, int sc) {
+    constexpr int PPR = WS / EP, NP = WR * PPR;   // pieces per row, in all
+    const int g0 = sr * ST - (W - 1), g1 = sc * ST - LP;
+#pragma unroll 4
+    for (int idx = threadIdx.x; idx < NP; idx += FWD_BLOCK) {
+      const int r = idx / PPR, c = (idx - r * PPR) * EP;
+      int gr = g0 + r, gc = g1 + c;
+      gr = gr < 0 ? gr + G : (gr >= G ? gr - G : gr);
+      gc = gc < 0 ? gc + G : (gc >= G ? gc - G : gc);
+      *reinterpret_cast<Piece*>(win + r * PITCH + c) =
+          *reinterpret_cast<const Piece*>(grid + (int64_t)gr * G + gc);
+    }
+  }
+  // first tap of a record whose cell is (c0, c1) of the square
+  __device__ static int cell(int c0, int c1) { return c0 * PITCH + c1 + (LP - (W - 1)); }
+};
+
+// whether the S x S tiles of square (sr, sc) hold any record
+template <int S>
+__device__ inline bool square_has_records(const int32_t* __restrict__ tile_off, int nt, int sr, int sc) {
+  int any = 0;
+  for (int k = 0; k < S; ++k) any |= tile_off[(sr * S + k) * nt + sc * S] != tile_off[(sr * S + k) * nt + sc * S + S];
+  return any != 0;
+}
+
 // Order of a square's records. Every lane of a wavefront reads its taps at the
 // same offsets from its own first cell, so two lanes meet on an LDS bank in
 // all of their taps or in none, by their first cells modulo the banks' cells
@@ -185,18 +227,15 @@ __global__ __launch_bounds__(FWD_BLOCK) void k_interp2d_sq(const Rec<real>* __re
   using elem = typename OUT::elem;
   constexpr int S = ST / T;             // tiles per edge of the square
   constexpr int L = 2 * W;
-  // the window's rows and columns; its columns start at a multiple of 16
-  // bytes, so that it is copied in 16-byte pieces (none straddles the grid's edge)
-  constexpr int EP = 16 / (int)sizeof(elem);
-  constexpr int LP = (W - 1 + EP - 1) / EP * EP;           // cells left of the square
-  constexpr int WR = ST + L - 1, WS = (LP + ST + W + EP - 1) / EP * EP;
+  using Win = Window<elem, W, ST>;
+  constexpr int WS = Win::PITCH;
   constexpr int SLOTS = 256 / (int)sizeof(elem);   // cells across the 64 banks
   constexpr int PER = SQ_CHUNK / FWD_BLOCK;
   struct Item {
     real f0, f1;
     int cell, src;
   };
-  __shared__ __align__(16) elem win[WR * WS];
+  __shared__ __align__(16) elem win[Win::WR * WS];
   __shared__ Item list[SQ_CHUNK];
   __shared__ unsigned long long round_mask[SQ_ROUNDS];   // slots with a record in round q
   __shared__ int round_base[SQ_ROUNDS];
@@ -206,22 +245,8 @@ __global__ __launch_bounds__(FWD_BLOCK) void k_interp2d_sq(const Rec<real>* __re
   const int nsq = nt / S;
   const int sq = (int)xcd_block(blockIdx.x, gridDim.x);
   const int sr = sq / nsq, sc = sq - (sq / nsq) * nsq;
-  int any = 0;
-  for (int k = 0; k < S; ++k) any |= tile_off[(sr * S + k) * nt + sc * S] != tile_off[(sr * S + k) * nt + sc * S + S];
-  if (!any) return;   // 30 % of the 4096^2 raster's squares lie outside its sector
-  struct alignas(16) Piece {
-    elem e[EP];
-  };
-  constexpr int PPR = WS / EP, NP = WR * PPR;   // pieces per row, in all
-  const int Gi = (int)G, g0 = sr * ST - (W - 1), g1 = sc * ST - LP;
-#pragma unroll 4
-  for (int idx = tid; idx < NP; idx += FWD_BLOCK) {
-    const int r = idx / PPR, c = (idx - r * PPR) * EP;
-    int gr = g0 + r, gc = g1 + c;
-    gr = gr < 0 ? gr + Gi : (gr >= Gi ? gr - Gi : gr);
-    gc = gc < 0 ? gc + Gi : (gc >= Gi ? gc - Gi : gc);
-    *reinterpret_cast<Piece*>(win + r * WS + c) = *reinterpret_cast<const Piece*>(grid + (int64_t)gr * Gi + gc);
-  }
+  if (!square_has_records<S>(tile_off, nt, sr, sc)) return;   // 30 % of the 4096^2 raster's lie outside its sector
+  Win::load(win, grid, (int)G, sr, sc);
   const real e2b = iexp((real)-2 * beta);
   for (int k = 0; k < S; ++k) {
     // the S tiles of this row of the square hold one contiguous record range
@@ -250,7 +275,7 @@ __global__ __launch_bounds__(FWD_BLOCK) void k_interp2d_sq(const Rec<real>* __re
         it[u].f0 = rec.f0;
         it[u].f1 = rec.f1;
         it[u].src = rec.src;
-        it[u].cell = (c0 + k * T) * WS + c1 + q * T + (LP - (W - 1));
+        it[u].cell = Win::cell(c0 + k * T, c1 + q * T);
         slot[u] = it[u].cell % SLOTS;
         rank[u] = atomicAdd(&cnt[slot[u]], 1);
       }
