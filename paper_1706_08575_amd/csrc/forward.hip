@@ -14,9 +14,9 @@
 //      workgroup per square of ST x ST cells (S x S tiles of the spread's
 //      binning, ST = 32, or 64 for tiles of 64 in float32) stages that square's
 //      window of H (its ST + 2W - 1 rows and columns, indices modulo G) in
-//      LDS with coalesced loads, lists each sample's home record (the record in the tile
-//      that holds its cell floor(u), so every sample is computed once) in an
-//      order without LDS bank conflicts, and walks the list one record per lane: the
+//      LDS with coalesced loads and takes each sample's home record (the record in the
+//      tile that holds its cell floor(u), so every sample is computed once), where
+//      it pays listed in an order without LDS bank conflicts, one per lane: the
 //      lane forms the 2W column factors once, and for each row adds
 //      the row's taps against them (two fused multiply-adds and one LDS read
 //      per tap) before scaling the row sum by the row factor (rows by the
@@ -167,13 +167,13 @@ struct DenOut {
 // cells fall on many banks: the samples of a pulse run down a column, and with the
 // plain width, a multiple of 8 or 16 cells at W = 4 and 8, the listed kernel found
 // only 4 or 2 slots there (float32, 2^20 samples on 512^2: W = 8 240 and 125 us, W =
-// 4 71 and 59, W = 6 97 and 88).
-template <class elem, int W, int ST>
+// 4 71 and 59, W = 6 97 and 88). ODD: an odd number of cells apart, written cell by cell.
+template <class elem, int W, int ST, bool ODD>
 struct Window {
   static constexpr int EP = 16 / (int)sizeof(elem);
   static constexpr int LP = (W - 1 + EP - 1) / EP * EP;           // cells left of the square
   static constexpr int WR = ST + 2 * W - 1, WS = (LP + ST + W + EP - 1) / EP * EP;
-  static constexpr int PITCH = WS + (WS / EP % 2 == 0 ? EP : 0);
+  static constexpr int PITCH = ODD ? WS | 1 : WS + (WS / EP % 2 == 0 ? EP : 0);
   struct alignas(16) Piece {
     elem e[EP];
   };
@@ -187,8 +187,13 @@ struct Window {
       int gr = g0 + r, gc = g1 + c;
       gr = gr < 0 ? gr + G : (gr >= G ? gr - G : gr);
       gc = gc < 0 ? gc + G : (gc >= G ? gc - G : gc);
-      *reinterpret_cast<Piece*>(win + r * PITCH + c) =
-          *reinterpret_cast<const Piece*>(grid + (int64_t)gr * G + gc);
+      const Piece v = *reinterpret_cast<const Piece*>(grid + (int64_t)gr * G + gc);
+      if constexpr (PITCH % EP == 0) {
+        *reinterpret_cast<Piece*>(win + r * PITCH + c) = v;
+      } else {
+#pragma unroll
+        for (int i = 0; i < EP; ++i) win[r * PITCH + c + i] = v.e[i];
+      }
     }
   }
   // first tap of a record whose cell is (c0, c1) of the square
@@ -227,7 +232,7 @@ __global__ __launch_bounds__(FWD_BLOCK) void k_interp2d_sq(const Rec<real>* __re
   using elem = typename OUT::elem;
   constexpr int S = ST / T;             // tiles per edge of the square
   constexpr int L = 2 * W;
-  using Win = Window<elem, W, ST>;
+  using Win = Window<elem, W, ST, false>;
   constexpr int WS = Win::PITCH;
   constexpr int SLOTS = 256 / (int)sizeof(elem);   // cells across the 64 banks
   constexpr int PER = SQ_CHUNK / FWD_BLOCK;
@@ -341,6 +346,65 @@ __global__ __launch_bounds__(FWD_BLOCK) void k_interp2d_sq(const Rec<real>* __re
   }
 }
 
+// The same without the lists: every thread takes the records in binning order,
+// skips those not at home, and has two rows of reads in flight, with no barrier in
+// the loop (which of the two runs: launch_interp_sq).
+template <class real, int W, int T, int ST, class OUT>
+__global__ __launch_bounds__(FWD_BLOCK) void k_interp2d_direct(const Rec<real>* __restrict__ recs,
+                                                               const int32_t* __restrict__ tile_off,
+                                                               const typename OUT::elem* __restrict__ grid,
+                                                               int64_t G, int nt, real beta, const OUT out) {
+  using elem = typename OUT::elem;
+  using Win = Window<elem, W, ST, true>;
+  constexpr int S = ST / T;             // tiles per edge of the square
+  constexpr int L = 2 * W;
+  __shared__ __align__(16) elem win[Win::WR * Win::PITCH];
+  const int nsq = nt / S;
+  const int sq = (int)xcd_block(blockIdx.x, gridDim.x);
+  const int sr = sq / nsq, sc = sq - (sq / nsq) * nsq;
+  if (!square_has_records<S>(tile_off, nt, sr, sc)) return;
+  Win::load(win, grid, (int)G, sr, sc);
+  __syncthreads();
+  const real e2b = iexp((real)-2 * beta);
+  for (int k = 0; k < S; ++k) {
+    const int id0 = (sr * S + k) * nt + sc * S;
+    const int rbeg = tile_off[id0], rend = tile_off[id0 + S];
+    int bnd[S > 1 ? S - 1 : 1];
+#pragma unroll
+    for (int q = 1; q < S; ++q) bnd[q - 1] = tile_off[id0 + q];
+    for (int r = rbeg + (int)threadIdx.x; r < rend; r += FWD_BLOCK) {
+      const Rec<real> rec = recs[r];
+      const int c0 = (int)(int16_t)(rec.c01 & 0xffff), c1 = rec.c01 >> 16;
+      if (c0 < 0 || c0 >= T || c1 < 0 || c1 >= T) continue;   // not the sample's home record
+      int q = 0;
+#pragma unroll
+      for (int m = 1; m < S; ++m) q += r >= bnd[m - 1];
+      real a[L], b[L];
+      gauss_taps<real, W>(rec.f0, beta, e2b, a);
+      gauss_taps<real, W>(rec.f1, beta, e2b, b);
+      const elem* p = win + Win::cell(c0 + k * T, c1 + q * T);
+      real ar = 0, ai = 0;
+#pragma unroll 2   // two rows of reads in flight (all 2W rows would hold them all in registers)
+      for (int j = 0; j < L; ++j) {
+        real sr_ = 0, si_ = 0;
+#pragma unroll
+        for (int c = 0; c < L; ++c) {
+          const elem v = p[j * Win::PITCH + c];
+          if constexpr (OUT::REAL) {
+            sr_ += b[c] * v;
+          } else {
+            sr_ += b[c] * v.x;
+            si_ += b[c] * v.y;
+          }
+        }
+        ar += a[j] * sr_;
+        if constexpr (!OUT::REAL) ai += a[j] * si_;
+      }
+      out.put(rec.src, ar, ai);
+    }
+  }
+}
+
 // 1D: one workgroup per tile, one thread per home record, 2W taps from global memory
 template <class real, int W>
 __global__ __launch_bounds__(FWD_BLOCK) void k_interp1d_tiles(const Rec<real>* __restrict__ recs,
@@ -378,31 +442,50 @@ __global__ __launch_bounds__(FWD_BLOCK) void k_interp1d_tiles(const Rec<real>* _
   }
 }
 
+// Which plans list their squares' records. Lists pay for their barriers with the
+// other workgroups of a compute unit, and by the taps of a record: with no more
+// squares than compute units, and up to W = 3, the direct kernel is faster
+// (float32 W = 6, lists and direct: half a million samples on 256^2, 256 squares,
+// 101 and 74 us, 40 000 there 29 and 26; 2^20 on 512^2, 1024 squares, 68 and 92,
+// W = 4 52 and 56, W = 3 45 and 44, W = 2 43 and 39; float64 W = 4 58 and 58). The
+// direct kernel's 16 x 16 taps in float64 are twice as slow at any size (2^19 on
+// 256^2 151 and 274).
+constexpr int SQ_MIN = 256;   // squares: one per compute unit
+template <class real, int W, class OUT>
+struct Lists {
+  static constexpr bool ALWAYS = sizeof(real) == 8 && W == 8 && !OUT::REAL, NEVER = W <= 3;
+};
+
 template <class real, int W, int ST, class OUT>
 static void launch_interp_sq(ftcg_plan p, const OUT out) {
-  const unsigned nsq = (unsigned)((p->G / ST) * (p->G / ST));
-  const auto* k = p->recs.as<Rec<real>>();
-  const auto* off = p->tile_off.as<int32_t>();
-  const auto* gr = p->grid.as<typename OUT::elem>();
-  const real beta = (real)p->beta;
+  using L = Lists<real, W, OUT>;
+  const int64_t nsq = (p->G / ST) * (p->G / ST);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nsq), dim3(FWD_BLOCK), 0, p->stream, p->recs.as<Rec<real>>(),
+                       p->tile_off.as<int32_t>(), p->grid.as<typename OUT::elem>(), p->G, (int)p->nt, (real)p->beta,
+                       out);
+    FTCG_HIP(hipGetLastError());
+  };
+  auto tiles = [&](auto tile) {
+    constexpr int T = decltype(tile)::value;
+    if constexpr (!L::NEVER) {
+      if (L::ALWAYS || nsq > SQ_MIN) {
+        go(k_interp2d_sq<real, W, T, ST, OUT>);
+        return;
+      }
+    }
+    if constexpr (!L::ALWAYS) go(k_interp2d_direct<real, W, T, ST, OUT>);
+  };
   switch (p->tile) {
-    case 16:
-      hipLaunchKernelGGL((k_interp2d_sq<real, W, 16, ST, OUT>), dim3(nsq), dim3(FWD_BLOCK), 0, p->stream, k, off, gr,
-                         p->G, (int)p->nt, beta, out);
-      break;
-    case 32:
-      hipLaunchKernelGGL((k_interp2d_sq<real, W, 32, ST, OUT>), dim3(nsq), dim3(FWD_BLOCK), 0, p->stream, k, off, gr,
-                         p->G, (int)p->nt, beta, out);
-      break;
+    case 16: tiles(std::integral_constant<int, 16>{}); break;
+    case 32: tiles(std::integral_constant<int, 32>{}); break;
     default:
       if constexpr (ST == 64) {
-        hipLaunchKernelGGL((k_interp2d_sq<real, W, 64, ST, OUT>), dim3(nsq), dim3(FWD_BLOCK), 0, p->stream, k, off, gr,
-                           p->G, (int)p->nt, beta, out);
+        tiles(std::integral_constant<int, 64>{});
         break;
       }
       throw StatusError{FTCG_EUNSUPPORTED};
   }
-  FTCG_HIP(hipGetLastError());
 }
 
 // edge of the squares of a 2D plan's interpolation, 0 where its tiles are too
