@@ -18,7 +18,7 @@
 //     that kernel); on gfx950 the float32 LDS atomic add retires about 0.33
 //     lanes per clock per CU and the 64-bit integer one about 9.9 (measured);
 //   * float64 plans, and float32 plans that ask for it: matrix products in
-//     float64 (k_spread2d_mm, one partial tile of 32 or 64 cells, W >= 5), else
+//     float64 (k_spread2d_mm, one partial tile of 32 or 64 cells, larger W), else
 //     float64 LDS words with ds_add_f64 (k_spread2d, k_spread1d); with
 //     lds_copies > 1 wave w accumulates into partial tile w % copies and the
 //     partial tiles are combined at the flush with compensated (TwoSum) addition.
@@ -259,24 +259,23 @@ __global__ __launch_bounds__(64 * MmTile<T>::NW, T == 64 ? 3 : 6) void k_spread2
 
 // Plans whose float64 accumulation runs through the kernel above: one partial tile
 // of 32 or 64 cells and a half-width W that fills the 16 x 16 blocks. A block
-// costs the same whatever part of it a footprint covers, so below W = 5 the
-// LDS-atomic kernel is faster (2^17 .. 2^20 samples, float64, products and
-// atomics: tile 32 W = 2 71 and 39 us, W = 3 80 and 65, W = 4 25 and 24 to 93 and
-// 94, W = 5 26 and 35; tile 64 W = 2 161 and 86, W = 4 50 and 40, W = 5 225 and 290).
-// With float32 factors, cheaper to form in each lane, tile 64 at W = 5 still loses on
-// dense rasters (2^19 samples on 256^2: 959 and 770 us; W = 6 1088 and 1129). At
-// tile 16 a block is the whole tile: one wavefront per workgroup and 19 KiB of LDS
-// leave too few of them.
-constexpr int MM_MIN_W = 5;
+// costs the same whatever part of it a footprint covers, so at small W the
+// LDS-atomic kernel is faster (2^17 .. 2^20 samples, products and atomics, us:
+// float64 tile 32 W = 2 71 and 39, W = 3 80 and 65, W = 4 24 and 24 to 92 and 94,
+// with 20 density iterations 631 and 663 to 2596 and 2806; tile 64 W = 2 161 and
+// 86, W = 4 50 and 40, W = 5 225 and 290). Float32 factors cost the lanes of the
+// atomics less and move each line up by one (tile 32 W = 4 21 and 21 to 82 and 80;
+// tile 64 W = 5, 2^19 samples on 256^2, 959 and 770). At tile 16 a block is the
+// whole tile: one wavefront per workgroup and 19 KiB of LDS leave too few of them.
+constexpr int MM_MIN_W = 4;
 static bool spreads_by_products(const ftcg_plan_s* p) {
-  if (p->dim != 2 || p->lds_copies != 1) return false;
-  return (p->tile == 32 && p->W >= MM_MIN_W) ||
-         (p->tile == 64 && p->W >= (p->dtype == FTCG_F64 ? MM_MIN_W : MM_MIN_W + 1));
+  if (p->dim != 2 || p->lds_copies != 1 || (p->tile != 32 && p->tile != 64)) return false;
+  return p->W >= MM_MIN_W + (p->tile == 64 ? 1 : 0) + (p->dtype == FTCG_F32 ? 1 : 0);
 }
 
 template <class real, int W, int SRC, class Val>
 static void launch_mm(ftcg_plan p, const Val* val, Val* grid) {
-  if constexpr (W >= MM_MIN_W) {
+  if constexpr (W >= MM_MIN_W + (sizeof(real) == 4 ? 1 : 0)) {
     auto go = [&](auto kernel, int nw) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)p->ntiles), dim3(64 * nw), 0, p->stream, p->recs.as<Rec<real>>(),
                          p->alpha_s.as<real>(), p->ws_sum.as<double>(), p->ws_inv.as<int32_t>(),
