@@ -1137,11 +1137,11 @@ void finish_deferred_weights(ftcg_plan p) {
   if (!captured) p->weights_deferred = false;
 }
 
-// samples per lane: the plan's tuning, else in 2D 2 from 2^20 samples (each
-// staged candidate then serves two pairs and one LDS atomic; measured on SAS
-// rasters of 2^20 and 2^23 samples: 0.371 against 0.402 ms and 1.76 against
-// 1.92 ms) and 1 below (2^17 samples: 0.042 against 0.068 ms, where the
-// lanes are too few); 1 in 1D
+// samples per lane: the plan's tuning, else in 2D 2 from 2^20 samples, or from
+// 600 000 with few candidates each (each staged candidate then serves two pairs
+// and one LDS atomic; measured on SAS rasters of 2^20 and 2^23 samples: 0.371
+// against 0.402 ms and 1.76 against 1.92 ms) and 1 below (2^17 samples: 0.042
+// against 0.068 ms, where the lanes are too few); 1 in 1D
 constexpr bool WEIGHT_SYMMETRIC = true;
 constexpr int SYM_MAX_WT = 2;   // samples per lane the symmetric kernel is built for
 
@@ -1152,12 +1152,18 @@ void run_plain_weights(ftcg_plan p) {
       p->dim == 2 ? (double)p->m / ((double)g.nb[0] * g.nb[1]) * (2 * g.span + 1) * (2 * g.span + 1) : 0.0;
   // samples per lane: 2 in 2D from 2^20 samples, but 1 when a sample has more
   // than about 10^4 candidates (3.5 M samples on a 256^2 image: 39 against
-  // 41 ms); with at most 10^3 candidates already from 600 000 samples, where
-  // the lanes are enough and the shared reciprocal and LDS atomic pay (2 against
-  // 1, four lanes each: 0.62 M samples on 1024^2 134 and 148 us, 0.88 M 232 and
-  // 272, 0.74 M on 2048^2 80 and 87; with 1160 candidates, 0.62 M on 512^2, 528
-  // and 400)
-  const int64_t two = cand <= 1e3 ? 600000 : int64_t(1) << 20;
+  // 41 ms); already from 600 000 samples with at most 350 candidates and from
+  // 750 000 with at most 550, where the lanes are enough and the shared reciprocal
+  // and LDS atomic pay. A sector's dense rows make the longest workgroups, and half
+  // the lanes lengthen them, so with more candidates or fewer samples one is the
+  // faster there. us, two samples and one, sectors, four lanes each: 600 000 samples
+  // with 77, 268, 431, 574, 905 candidates 67 and 70, 122 and 145, 246 and 203, 325
+  // and 265, 462 and 393; 800 000 with 103, 332, 472, 643, 1186: 91 and 98, 200 and
+  // 239, 285 and 319, 465 and 365, 734 and 661; 500 000 with 64, 223: 50 and 55, 136
+  // and 109. (Rasters of even density gain from two samples at 150 000 already, 85
+  // and 94 us at 688 candidates; the box does not tell them apart.)
+  const double few = p->m >= 750000 ? 550 : 350;
+  const int64_t two = cand <= few ? 600000 : int64_t(1) << 20;
   const int wt = p->w_samples ? p->w_samples : (p->dim == 2 && p->m >= two && cand <= 1e4 ? 2 : 1);
   if (p->dim == 2) {
     // lanes per sample group: the plan's tuning, else 4 below 2^21 samples
