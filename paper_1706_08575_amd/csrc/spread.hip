@@ -1024,12 +1024,11 @@ bool ready_weights(ftcg_plan p) {
   if (!p->sums_ready) return false;
   const bool forms = p->dim == 2 && (p->accum == ACCUM_FIXED || spreads_by_products(p));
   if (forms) {
-    if (being_captured(p)) return true;
-    if (!p->weights_deferred) return false;
-    if (p->deferred_spreads < DEFERRED_SPREADS) {
+    if (p->weights_deferred && p->deferred_spreads < DEFERRED_SPREADS) {
       ++p->deferred_spreads;
       return true;
     }
+    if (being_captured(p)) return true;
   }
   finish_deferred_weights(p);
   return false;
