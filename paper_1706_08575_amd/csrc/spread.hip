@@ -141,14 +141,18 @@ __global__ __launch_bounds__(64 * MmTile<T>::NW, T == 64 ? 3 : 6) void k_spread2
       const Rec<real> rec = next;
       next = recs[min(cb + MM_CH + lane, end - 1)];
       {
-        const int part = wave;           // rows, columns: two halves each
-        const int j0 = (part & 1) * W;   // half of the axis: factors j0 .. j0 + W - 1
-        const real d = (real)(j0 + 1 - W) - (part < 2 ? rec.f0 : rec.f1);
-        real e = kexp(-beta * d * d), q = kexp(-beta * (2 * d + 1));
+        // rows, columns: two halves each, from the sample's cell (factor W - 1)
+        // outward: the large taps carry the exponential's error at a small argument
+        const int part = wave;
+        const bool up = part & 1;        // factors W, W + 1, .. 2W - 1; else W - 1, .. 0
+        const int j0 = up ? W : W - 1, step = up ? PITCH : -PITCH;
+        const real d = (up ? (real)1 : (real)0) - (part < 2 ? rec.f0 : rec.f1);
+        real e = kexp(-beta * d * d), q = kexp(up ? -beta * (2 * d + 1) : -beta * (1 - 2 * d));
         if (part < 2) {
+          double* to = frow + j0 * PITCH + lane;
 #pragma unroll
           for (int j = 0; j < W; ++j) {
-            frow[(j0 + j) * PITCH + lane] = (double)e;
+            to[j * step] = (double)e;
             e *= q;
             q *= e2b;
           }
@@ -172,12 +176,13 @@ __global__ __launch_bounds__(64 * MmTile<T>::NW, T == 64 ? 3 : 6) void k_spread2
             fin = isfinite(v.x) && isfinite(v.y);
           }
           if (part == 2) finite[lane] = fin ? 1 : 0;
+          fac* to = fcol + j0 * PITCH + lane;
 #pragma unroll
           for (int j = 0; j < W; ++j) {
             if constexpr (REAL)
-              fcol[(j0 + j) * PITCH + lane] = (double)e * (double)v;
+              to[j * step] = (double)e * (double)v;
             else
-              fcol[(j0 + j) * PITCH + lane] = make_double2((double)e * (double)v.x, (double)e * (double)v.y);
+              to[j * step] = make_double2((double)e * (double)v.x, (double)e * (double)v.y);
             e *= q;
             q *= e2b;
           }
@@ -263,14 +268,15 @@ __global__ __launch_bounds__(64 * MmTile<T>::NW, T == 64 ? 3 : 6) void k_spread2
 // LDS-atomic kernel is faster (2^17 .. 2^20 samples, products and atomics, us:
 // float64 tile 32 W = 2 71 and 39, W = 3 80 and 65, W = 4 24 and 24 to 92 and 94,
 // with 20 density iterations 631 and 663 to 2596 and 2806; tile 64 W = 2 161 and
-// 86, W = 4 50 and 40, W = 5 225 and 290). Float32 factors cost the lanes of the
-// atomics less and move each line up by one (tile 32 W = 4 21 and 21 to 82 and 80;
-// tile 64 W = 5, 2^19 samples on 256^2, 959 and 770). At tile 16 a block is the
-// whole tile: one wavefront per workgroup and 19 KiB of LDS leave too few of them.
+// 86, W = 4 50 and 40, W = 5 225 and 290). With float32 factors, which cost the
+// lanes of the atomics less, W = 4 is the atomics' too (16 and 15 to 82 and 80), and
+// so would be W = 5 of a dense raster in few tiles of 64 (2^19 samples on 256^2: 959
+// and 770; on 1024^2 98 and 152). At tile 16 a block is the whole tile: one
+// wavefront per workgroup and 19 KiB of LDS leave too few of them.
 constexpr int MM_MIN_W = 4;
 static bool spreads_by_products(const ftcg_plan_s* p) {
   if (p->dim != 2 || p->lds_copies != 1 || (p->tile != 32 && p->tile != 64)) return false;
-  return p->W >= MM_MIN_W + (p->tile == 64 ? 1 : 0) + (p->dtype == FTCG_F32 ? 1 : 0);
+  return p->W >= (p->tile == 32 && p->dtype == FTCG_F64 ? MM_MIN_W : MM_MIN_W + 1);
 }
 
 template <class real, int W, int SRC, class Val>
