@@ -342,28 +342,37 @@ __global__ __launch_bounds__(SPREAD_BLOCK) void k_spread2d(const Rec<real>* __re
       if (col >= 0 && col < T) {
         const real d1 = (real)(i - W + 1) - rec.f1;
         const real w1 = REAL ? kexp(-beta * d1 * d1) : kexp(-beta * d1 * d1) * alpha_s[r];
-        const real d0 = (real)(1 - W) - rec.f0;
-        const real w0 = kexp(-beta * d0 * d0);
-        real q = kexp(-beta * (2 * d0 + 1));
-        real pr, pi = 0;
-        if constexpr (REAL) {
-          pr = v * w1 * w0;
-        } else {
-          pr = v.x * w1 * w0;
-          pi = v.y * w1 * w0;
-        }
-        const int row0 = c0 - W + 1;
-        double* pre = mine + col;
-#pragma unroll
-        for (int j = 0; j < L; ++j) {
-          const int row = row0 + j;
-          if (row >= 0 && row < T) {
-            lds_add(pre + row * TP, (double)pr);
-            if constexpr (!REAL) lds_add(pre + plane + row * TP, (double)pi);
+        double* pre = mine + (c0 - W + 1) * TP + col;
+        // rows j0, j0 + dir, .. (n of them), the first at distance d from the sample
+        // and the others farther (or, dir 1 and d < 0, through it)
+        auto walk = [&](int j0, int dir, auto n, real d) {
+          real e = w1 * kexp(-beta * d * d), q = kexp(-beta * (2 * d + 1));
+          real pr, pi = 0;
+          if constexpr (REAL) {
+            pr = v * e;
+          } else {
+            pr = v.x * e;
+            pi = v.y * e;
           }
-          pr *= q;
-          if constexpr (!REAL) pi *= q;
-          q *= e2b;
+#pragma unroll
+          for (int i = 0; i < decltype(n)::value; ++i) {
+            const int j = j0 + dir * i, row = c0 - W + 1 + j;
+            if (row >= 0 && row < T) {
+              lds_add(pre + j * TP, (double)pr);
+              if constexpr (!REAL) lds_add(pre + plane + j * TP, (double)pi);
+            }
+            pr *= q;
+            if constexpr (!REAL) pi *= q;
+            q *= e2b;
+          }
+        };
+        // float32 taps from the sample's cell outward: from the footprint's edge on
+        // every row would carry the exponential's error at beta W^2
+        if constexpr (std::is_same<real, float>::value) {
+          walk(W - 1, -1, std::integral_constant<int, W>{}, rec.f0);
+          walk(W, 1, std::integral_constant<int, W>{}, 1 - rec.f0);
+        } else {
+          walk(0, 1, std::integral_constant<int, L>{}, (real)(1 - W) - rec.f0);
         }
       }
     }
