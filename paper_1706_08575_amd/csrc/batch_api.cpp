@@ -192,6 +192,7 @@ ftcg_status ftcg_batch_create(ftcg_batch_s** out, int n_items, const int64_t* n,
       const int64_t nn[2] = {n[i], n[i]};
       ftcg_status s = ftcg_plan_create(&p, 2, nn, half_width, sigma, FTCG_F32, wmode, R, hip_stream);
       if (s != FTCG_OK) throw StatusError{s};
+      p->in_batch = n_items > 1;
       b->plans.push_back(p);
       b->n.push_back(n[i]);
       s = ftcg_plan_set_tuning(p, b->tile, FTCG_ACCUM_FIXED, 1);

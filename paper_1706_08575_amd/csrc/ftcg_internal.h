@@ -445,6 +445,7 @@ struct ftcg_plan_s {
   int deferred_spreads = 0;   // spreads that formed the weights so far
   ftcg::WBinGeom wgeom{};
   bool have_wbins = false;
+  bool in_batch = false;      // its set_points runs beside those of a batch's other items
   bool weights_only = false;  // internal plans that only compute weights (no tile binning)
 
   // banded coefficient matrix C (FTCG_W_BAND)

@@ -1161,8 +1161,11 @@ void run_plain_weights(ftcg_plan p) {
   // and 265, 462 and 393; 800 000 with 103, 332, 472, 643, 1186: 91 and 98, 200 and
   // 239, 285 and 319, 465 and 365, 734 and 661; 500 000 with 64, 223: 50 and 55, 136
   // and 109. (Rasters of even density gain from two samples at 150 000 already, 85
-  // and 94 us at 688 candidates; the box does not tell them apart.)
-  const double few = p->m >= 750000 ? 550 : 350;
+  // and 94 us at 688 candidates; the box does not tell them apart.) The items of a
+  // batch share the chip, where the longest workgroups matter less than the whole work:
+  // 10^3 candidates there (16 pings of 2^16 .. 2^20 samples, one of them 673 535 with
+  // 888: 9.51 and 9.66 ms).
+  const double few = p->in_batch ? 1000 : p->m >= 750000 ? 550 : 350;
   const int64_t two = cand <= few ? 600000 : int64_t(1) << 20;
   const int wt = p->w_samples ? p->w_samples : (p->dim == 2 && p->m >= two && cand <= 1e4 ? 2 : 1);
   if (p->dim == 2) {
