@@ -133,7 +133,8 @@ __device__ inline void gauss_taps(real f, real beta, real e2b, real (&out)[2 * W
 
 // What a square's kernel does with a sample's sum: the forward transform
 // stores it (FwdOut); a density iteration, whose grid is real, divides the
-// sample's weight by it (DenOut).
+// sample's weight by it, or (DEN_SUM) leaves it in the values for a pass of its
+// own (DenOut).
 template <class real>
 struct FwdOut {
   using elem = typename CxI<real>::t;   // grid cells
@@ -153,11 +154,15 @@ struct DenOut {
   double* w;
   real* val;
   double scale;
-  int last;
+  DenStep step;
   __device__ void put(int src, real re, real) const {
+    if (step == DEN_SUM) {
+      val[src] = re;
+      return;
+    }
     const double x = w[src] / (double)re;
-    w[src] = last ? x * scale : x;
-    if (!last) val[src] = (real)x;
+    w[src] = step == DEN_LAST ? x * scale : x;
+    if (step == DEN_NEXT) val[src] = (real)x;
   }
 };
 
@@ -562,21 +567,21 @@ void interpolate_grid(ftcg_plan p, void* out) {
 }
 
 template <class real, int W>
-static void launch_interp_density(ftcg_plan p, double* w, void* val, double scale, bool last) {
-  launch_interp_squares<real, W>(p, DenOut<real>{w, static_cast<real*>(val), scale, last ? 1 : 0});
+static void launch_interp_density(ftcg_plan p, double* w, void* val, double scale, DenStep step) {
+  launch_interp_squares<real, W>(p, DenOut<real>{w, static_cast<real*>(val), scale, step});
 }
 
-void interpolate_density(ftcg_plan p, double* w, void* val, double scale, bool last) {
+void interpolate_density(ftcg_plan p, double* w, void* val, double scale, DenStep step) {
   auto go = [&](auto real_tag) {
     using real = decltype(real_tag);
     switch (p->W) {
-      case 2: launch_interp_density<real, 2>(p, w, val, scale, last); break;
-      case 3: launch_interp_density<real, 3>(p, w, val, scale, last); break;
-      case 4: launch_interp_density<real, 4>(p, w, val, scale, last); break;
-      case 5: launch_interp_density<real, 5>(p, w, val, scale, last); break;
-      case 6: launch_interp_density<real, 6>(p, w, val, scale, last); break;
-      case 7: launch_interp_density<real, 7>(p, w, val, scale, last); break;
-      case 8: launch_interp_density<real, 8>(p, w, val, scale, last); break;
+      case 2: launch_interp_density<real, 2>(p, w, val, scale, step); break;
+      case 3: launch_interp_density<real, 3>(p, w, val, scale, step); break;
+      case 4: launch_interp_density<real, 4>(p, w, val, scale, step); break;
+      case 5: launch_interp_density<real, 5>(p, w, val, scale, step); break;
+      case 6: launch_interp_density<real, 6>(p, w, val, scale, step); break;
+      case 7: launch_interp_density<real, 7>(p, w, val, scale, step); break;
+      case 8: launch_interp_density<real, 8>(p, w, val, scale, step); break;
       default: throw StatusError{FTCG_EUNSUPPORTED};
     }
   };

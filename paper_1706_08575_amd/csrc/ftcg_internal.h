@@ -507,7 +507,8 @@ constexpr int64_t WROW_CNT_ZERO = 4100;   // bin-row counters cleared by the inp
 constexpr int CHECK_PARTS = 256;         // input-check workgroups at most: one per CU. Each adds an arrival at
                                           // one ticket, and the last folds all partials (2^23 points 50 us
                                           // with 1024 of them, 44 with 256; 2^20 14.9 and 12.4)
-// returns the number of partial records (5 words each) written to part
+// one pass over the points: the check's result to p->geo and p->host_geo, numbered
+// seq, and the counters zero_a and zero_b cleared
 void launch_check_points(ftcg_plan p, const double* k, int64_t m, int seq, int32_t* zero_a, int64_t zero_na,
                          int32_t* zero_b, int64_t zero_nb);
 void bin_points_k(ftcg_plan p, const double* k);   // fills recs, alpha_s, tile_off
@@ -548,8 +549,10 @@ void interpolate_grid(ftcg_plan p, void* out);      // out_j = taps of sample j 
 bool interp_in_squares(const ftcg_plan_s* p);
 bool density_real(const ftcg_plan_s* p);
 void spread_real(ftcg_plan p, const void* val, void* grid);
-// d_j from the real grid, then w_j <- w_j / d_j (times scale in the last iteration) and val_j = w_j
-void interpolate_density(ftcg_plan p, double* w, void* val, double scale, bool last);
+// d_j from the real grid, then w_j <- w_j / d_j (times scale in the last iteration) and
+// val_j = w_j; or (DEN_SUM) val_j = d_j
+enum DenStep { DEN_NEXT, DEN_LAST, DEN_SUM };
+void interpolate_density(ftcg_plan p, double* w, void* val, double scale, DenStep step);
 void run_density_weights(ftcg_plan p);              // iterative density compensation into p->alpha
 // dense frame approximation of the raster k (m samples) into image (float64 plans)
 void frame_approx(ftcg_plan p, int64_t m, const double* k, const void* fhat, void* image);
