@@ -207,7 +207,7 @@ ftcg_status ftcg_plan_set_density_iterations(ftcg_plan plan, int iters);
  * the band J(n) = {n - r + 1, ..., n + r - 1} taken in the caller's sample
  * order (for a raster acquired pulse by pulse, neighbouring samples of a
  * pulse). Column n solves the normal equations of its least-squares problem
- * by a float64 Cholesky factorisation; r = 1 gives the diagonal weights of
+ * by a float64 Gauss-Jordan elimination; r = 1 gives the diagonal weights of
  * FTCG_W_PLAIN.
  *   ftcg_plan_set_band : r in 1..16 (default 1); takes effect at the next
  *                        ftcg_set_points. FTCG_ESTATE for other weight modes.
@@ -270,10 +270,12 @@ ftcg_status ftcg_plan_info(ftcg_plan plan, int64_t* grid_size, int64_t* n_record
  *                      records, so a larger tile of a dense raster has a coarser
  *                      quantum (54 samples per pixel: 4.5e-6 relative L2 of the
  *                      image at tile 32, 1.3e-5 at 64).
- *   FTCG_ACCUM_F64   : taps accumulated with float64 LDS atomics (the default
- *                      and only mode of float64 plans); lds_copies > 1 gives
- *                      each wavefront its own partial tile, combined at the
- *                      flush with compensated (TwoSum) addition. */
+ *   FTCG_ACCUM_F64   : taps accumulated in float64 (the default and only mode
+ *                      of float64 plans): as matrix products on 2D tiles of
+ *                      32 and 64 with one partial tile and W >= 5 (tile 32 in
+ *                      float64 plans: 4), else with LDS atomics; lds_copies > 1
+ *                      gives each wavefront its own partial tile, combined at
+ *                      the flush with compensated (TwoSum) addition. */
 typedef FTCG_ENUM { FTCG_ACCUM_FIXED = 0, FTCG_ACCUM_F64 = 1 } ftcg_accum;
 
 /* Tuning knobs (take effect at the next ftcg_set_points; the points must be
@@ -334,7 +336,10 @@ ftcg_status ftcg_plan_set_weight_tuning(ftcg_plan plan, int samples_per_lane, in
  * (host arrays of FTCG_TIMING_STEPS entries; unused entries are 0), then
  * resets the sums. A step can be timed in several intervals per call (step 0:
  * the input check, then the binning after the host has read the check's
- * result; the host's wait in between is in no step). */
+ * result; the host's wait in between is in no step). 1D FTCG_W_PLAIN plans take
+ * up to 4096 samples through one launch, timed as step 0: steps 1 and 5 count
+ * nothing there. Step 8 also holds the finish that the third spread of a point
+ * set, ftcg_get_weights or a spread that reads the records' weights runs first. */
 #define FTCG_TIMING_STEPS 16
 ftcg_status ftcg_plan_enable_timing(ftcg_plan plan, int enable);
 ftcg_status ftcg_plan_timing(ftcg_plan plan, double* ms, int64_t* count);

@@ -215,8 +215,9 @@ void set_points_begin(ftcg_plan p, int64_t m, const double* k_dev) {
 // event, its signal and the wait for the rest of the launch (n = 256, G = 512,
 // points and image: 22 us against 30). The other paths have binning passes in
 // the queue meanwhile and keep the event (reading instead: 1 to 2 % on 2D
-// rasters of a few thousand samples, nothing above). After 2 ms without it, other work being ahead on the stream or a
-// launch having failed, the stream's end decides.
+// rasters of a few thousand samples, nothing above). After 2 ms without it, other
+// work being ahead on the stream or a launch having failed, the stream's end
+// decides.
 static void wait_check(ftcg_plan p, int seq) {
   const auto t0 = std::chrono::steady_clock::now();
   for (int i = 0; __atomic_load_n(&p->host_geo->seq, __ATOMIC_ACQUIRE) != seq; ++i) {

@@ -227,7 +227,7 @@ __device__ inline void knn_rings(const WSample<2>* __restrict__ ss, const int32_
 }
 
 // keys (float32 d2 bits << 32 | caller index) of the 16 nearest box
-// neighbours of sample (x, jself); empty slots stay ~0. Bins are visited in
+// neighbours of sample (x, jself); empty slots stay infinite. Bins are visited in
 // rings of growing Chebyshev distance around the sample's bin, until every
 // unvisited sample is farther than the 16th (knn_done).
 __device__ inline void knn_search(const WSample<2>* __restrict__ ss, const int32_t* __restrict__ sidx,
