@@ -435,10 +435,10 @@ ftcg_status ftcg_batch_create(ftcg_batch* out, int n_items, const int64_t* n_hos
                               double oversampling, ftcg_wmode wmode, double weight_radius, void* hip_stream);
 ftcg_status ftcg_batch_destroy(ftcg_batch batch);
 
-/* tile edge (16/32/64/128, default 32; larger ones have a coarser quantum, see
- * FTCG_ACCUM_FIXED), records per task (>= 64, default 4096), workgroups of the
- * persistent launch (default 8 per CU), graph replay on/off (default on). The
- * points must be set again afterwards. */
+/* tile edge (16/32/64/128, default 32, at most the smallest item's grid; larger
+ * ones have a coarser quantum, see FTCG_ACCUM_FIXED), records per task (>= 64,
+ * default 4096), workgroups of the persistent launch (default 8 per CU), graph
+ * replay on/off (default on). The points must be set again afterwards. */
 ftcg_status ftcg_batch_set_tuning(ftcg_batch batch, int tile, int64_t chunk_records, int persistent_blocks,
                                   int use_graph);
 

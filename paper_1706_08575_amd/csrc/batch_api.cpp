@@ -64,6 +64,23 @@ void enqueue_execute(ftcg_batch_s* b, hipStream_t s) {
   b->stream = keep;
 }
 
+// The tile edge of all items: the requested one, but no larger than the smallest
+// item's grid. (A plan clamps its own tile to its grid; the batch's kernels have one
+// tile for all items and would write past such a grid.) Grids are powers of two from
+// 2 W and 16 up.
+int fitting_tile(const ftcg_batch_s* b, int tile) {
+  for (ftcg_plan p : b->plans) tile = (int)std::min<int64_t>(tile, p->G);
+  return tile;
+}
+
+void tune_plans(ftcg_batch_s* b, int tile) {
+  for (ftcg_plan p : b->plans) {
+    const ftcg_status s = ftcg_plan_set_tuning(p, tile, FTCG_ACCUM_FIXED, 1);
+    if (s != FTCG_OK) throw StatusError{s};
+  }
+  b->tile = tile;
+}
+
 // build the tile and task tables from the item plans' tile offsets
 void build_tables(ftcg_batch_s* b) {
   std::vector<BatchTile> tiles;
@@ -195,9 +212,8 @@ ftcg_status ftcg_batch_create(ftcg_batch_s** out, int n_items, const int64_t* n,
       p->in_batch = n_items > 1;
       b->plans.push_back(p);
       b->n.push_back(n[i]);
-      s = ftcg_plan_set_tuning(p, b->tile, FTCG_ACCUM_FIXED, 1);
-      if (s != FTCG_OK) throw StatusError{s};
     }
+    tune_plans(b, fitting_tile(b, b->tile));
     b->items.resize(n_items);
     b->m.assign(n_items, 0);
     b->items_dev.ensure(sizeof(BatchItem) * n_items);
@@ -274,11 +290,7 @@ ftcg_status ftcg_batch_set_tuning(ftcg_batch_s* b, int tile, int64_t chunk_recor
   if (tile < 2 * b->W) return FTCG_EINVAL;
   if (chunk_records < 64 || persistent_blocks < 1 || persistent_blocks > 65536) return FTCG_EINVAL;
   return guard([&] {
-    for (ftcg_plan p : b->plans) {
-      ftcg_status s = ftcg_plan_set_tuning(p, tile, FTCG_ACCUM_FIXED, 1);
-      if (s != FTCG_OK) throw StatusError{s};
-    }
-    b->tile = tile;
+    tune_plans(b, fitting_tile(b, tile));
     b->chunk = chunk_records;
     b->persistent_blocks = persistent_blocks;
     b->use_graph = use_graph != 0;
